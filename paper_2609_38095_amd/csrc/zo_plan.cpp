@@ -50,17 +50,18 @@ int check_params(const void* params, zo_dtype dt, uint64_t offset, uint64_t n) {
   return ZO_OK;
 }
 
-// Full row groups need the address of global element 0 (params shifted back by offset
-// elements; the subtraction may wrap, only its alignment is used) to be 16-byte aligned, so
-// that every group vector is an aligned 16 bytes.
+// The address of global element 0 (params shifted back by offset elements; the subtraction may
+// wrap, only its alignment is used) is 16-byte aligned when every group vector is.
 bool groups_aligned(const void* params, uint64_t offset, size_t elem) {
   return ((reinterpret_cast<uintptr_t>(params) - static_cast<uintptr_t>(offset * elem)) & 15u) == 0;
 }
 
 // The addresses are device addresses: they are only ever offset here, never dereferenced, and
-// are carried as integers until the plan holds them. Without full row groups n must be at most
-// kPieceElems (plan_segments splits larger tensors), so that the edge-tile counts fit 32 bits.
-Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t chunk_groups) {
+// are carried as integers until the plan holds them. Full row groups sit at
+// any weight's address with any_alignment; without it misaligned storage has none, and n must then
+// be at most kPieceElems (plan_segments splits larger tensors), so that the edge-tile counts fit
+// 32 bits.
+Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t chunk_groups, bool any_alignment) {
   Plan pl{};
   pl.base = static_cast<char*>(params);
   pl.lo = offset;
@@ -68,7 +69,7 @@ Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t 
   if (n == 0) return pl;
   const uintptr_t addr = reinterpret_cast<uintptr_t>(params);
   uint64_t head_end = pl.hi, tail_begin = pl.hi;
-  if (groups_aligned(params, offset, elem)) {
+  if (any_alignment || groups_aligned(params, offset, elem)) {
     const uint64_t g_lo = ceil_div(pl.lo, kGroupElems), g_hi = pl.hi / kGroupElems;
     if (g_lo < g_hi) {  // g_hi - g_lo < 2^30: n < ZO_N_MAX is checked first
       pl.g_lo = g_lo;

@@ -21,9 +21,11 @@ constexpr uint32_t kDefaultMaxBlocks = 65536;
 constexpr uint32_t kSegsPerLaunch = 64;            // segments per batched launch (kernel arguments, ~5 KiB)
 constexpr uint64_t kMaxLaunchChunks = 1ull << 31;  // chunks per launch: 32-bit indices with room for the stride
 constexpr uint64_t kMaxLaunchEdges = 1ull << 31;   // edge tiles per launch, likewise
-// Storage that is not 16-byte aligned relative to the global index has no full row groups:
-// every element takes the element-wise path, one tile per lane. Such a tensor is planned in
-// pieces of at most kPieceElems elements (2^30 tiles), so that edge-tile counts stay 32-bit.
+// Planned without any_alignment, storage that is not 16-byte aligned relative to the global
+// index has no full row groups: every element takes the element-wise path, one tile per lane,
+// and the tensor is planned in pieces of at most kPieceElems elements (2^30 tiles), so that
+// edge-tile counts stay 32-bit. The sweeps plan with any_alignment (full row groups wherever the
+// storage lies); kernels that need aligned vectors plan without it.
 constexpr uint64_t kPieceElems = 1ull << 34;
 constexpr uint64_t kStreamBytes = 256ull << 20;    // sweeps at least this large stream (above the Infinity Cache)
 
@@ -104,7 +106,7 @@ struct Shape {
 };
 
 // Whether global element 0 of a tensor stored from params with global offset `offset` would
-// sit at a 16-byte boundary, which the full row groups need.
+// sit at a 16-byte boundary, i.e. whether the vectors of its row groups are 16-byte aligned.
 bool groups_aligned(const void* params, uint64_t offset, size_t elem);
 
 // Validation (ZO_OK or the status the calls return; nothing is launched on an error).
@@ -117,7 +119,8 @@ Probe make_probe(uint32_t k, float eps);
 Gen make_gen(uint64_t seed, uint32_t step);
 
 // Planning.
-Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t chunk_groups);
+Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t chunk_groups,
+               bool any_alignment = false);
 uint32_t plan_chunks(const Plan& pl, uint32_t chunk_groups);
 uint32_t grid_for(uint64_t work_items, uint64_t per_block, uint32_t block, bool sized = false);
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w);
@@ -157,14 +160,14 @@ uint32_t plans_grid(const Plans<N>& ps, const Shape& sh) {
 }
 
 // A list of tensors in launches of up to N plans: calls launch(plans) for every batch.
-// Segments with n = 0 are skipped; a segment without full row groups is planned in pieces of
-// kPieceElems; a batch is closed before its chunk or edge-tile count would reach 2^31.
+// Segments with n = 0 are skipped; without any_alignment, a segment that is not 16-byte aligned
+// is planned in pieces of kPieceElems; a batch is closed before its chunk or edge-tile count would reach 2^31.
 // `streams`: the streams of one workgroup of the launches (the chunk alignment of add_plan).
 // Returns the first status launch() returns other than ZO_OK, else ZO_OK. The list must have
 // passed check_segments.
 template <int N, class Launch>
 int plan_segments(const zo_segment* segs, uint32_t n_segs, size_t elem, uint32_t chunk_groups, uint32_t streams,
-                  Launch launch) {
+                  Launch launch, bool any_alignment = false) {
   Plans<N> ps{};
   ps.chunk_groups = chunk_groups;
   auto add = [&](const Plan& pl) {
@@ -186,11 +189,11 @@ int plan_segments(const zo_segment* segs, uint32_t n_segs, size_t elem, uint32_t
   };
   for (uint32_t i = 0; i < n_segs; ++i) {
     const zo_segment& sg = segs[i];
-    const uint64_t piece = groups_aligned(sg.params, sg.offset, elem) ? sg.n : kPieceElems;
+    const uint64_t piece = any_alignment || groups_aligned(sg.params, sg.offset, elem) ? sg.n : kPieceElems;
     for (uint64_t done = 0; done < sg.n; done += piece) {
       const uint64_t m = sg.n - done < piece ? sg.n - done : piece;
       void* at = reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(sg.params) + static_cast<uintptr_t>(done * elem));
-      const int rc = add(make_plan(at, sg.offset + done, m, elem, chunk_groups));
+      const int rc = add(make_plan(at, sg.offset + done, m, elem, chunk_groups, any_alignment));
       if (rc != ZO_OK) return rc;
     }
   }

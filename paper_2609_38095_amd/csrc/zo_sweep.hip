@@ -590,12 +590,12 @@ int run_one(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t s
   hipStream_t st = static_cast<hipStream_t>(stream);
   const zo_segment seg{params, offset, n};
   (void)hipGetLastError();
-  // one launch (several only for a tensor of more than kPieceElems weights without full row groups)
+  // one launch, full row groups at any alignment
   return plan_segments<1>(&seg, 1, sizeof(typename S::storage), sh.chunk_groups, streams_per_block(sh),
                           [&](const Plans<1>& ps) {
     launch_sweep<S>(ps, gen, w, sh, st);
     return launch_status();
-  });
+  }, true);
 }
 
 int run_one_dt(void* params, zo_dtype dtype, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step,
@@ -628,7 +628,7 @@ int run_segments(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_
                                        streams_per_block(sh), [&](const Plans<kSegsPerLaunch>& ps) {
                                          launch_sweep<S>(ps, gen, w, sh, st);
                                          return launch_status();
-                                       });
+                                       }, true);
 }
 
 int run_segments_dt(const zo_segment* segs, uint32_t n_segs, zo_dtype dtype, uint64_t seed, uint32_t step,
