@@ -113,7 +113,11 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 // larger workgroups that share one set of spread tables. The shapes below are the fastest of
 // those measured (A/B on one box) on OPT-13B shaped bf16 buffers (K <= 16), OPT-30B (K = 32),
 // OPT-1.3B and Qwen3-8B (K = 60-64) and 3 G-element fp32 buffers:
-//   perturb, one or two probes: 256 threads, one workgroup per CU;
+//   perturb, one or two probes: 256 threads, one workgroup per CU; one fp32 probe: 128 threads, one
+//     chunk per wave (1.3 G weights: 1,751 -> 1,591 us, 6.01 -> 6.62 TB/s, the rate of a plain
+//     read-modify-write; a row group is twice bf16's bytes, so two waves keep as much in flight as
+//     four do there; 64, 192 and 512 threads, 16 and 64 KiB chunks, one and three groups ahead and
+//     other paces 1 to 50% slower; bf16 with 128 threads 38% and two fp32 probes 8 to 30% slower);
 //   update, one bf16 group: one workgroup per CU, one chunk per wave (OPT-30B K = 8: 6.19 ->
 //     6.53 TB/s), paced at four outstanding memory operations as the perturb (+0.5%);
 //   update, two bf16 groups: 512 threads, two waves per stream, one chunk per stream, 32-copy
@@ -156,7 +160,12 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
     // one chunk per wave: bf16 with one probe or two in one group, fp32 with two probes
     const bool one_group_bf16 = elem == 2 && (!w.two || w.a.group == w.b.group);
     const bool two_probes_fp32 = w.two && elem == 4;
-    return Shape{chunk, 1, one_group_bf16 || two_probes_fp32 ? 1u : 0u};
+    Shape sh{chunk, 1, one_group_bf16 || two_probes_fp32 ? 1u : 0u};
+    if (elem == 4 && !w.two) {
+      sh.block = 128;
+      sh.chunks_per_wave = 1;
+    }
+    return sh;
   }
   if (w.restore && !w.fold) return short_chunks;
   const uint32_t g = w.n_groups;

@@ -484,15 +484,21 @@ void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shap
   };
   if (!w.update) {
     const size_t pad = occupancy_lds(cap, 0);
-    auto go = [&](auto kernel, Probe b) {
+    auto go = [&](auto kernel, Probe b, uint32_t block = kBlock) {
       allow_lds(kernel, pad);
-      kernel<<<grid_of(kBlock, 1), dim3(kBlock), pad, st>>>(ps, gen, w.a, b);
+      kernel<<<grid_of(block, 1), dim3(block), pad, st>>>(ps, gen, w.a, b);
     };
     // paced when the generator work per byte is lightest: one probe group, or fp32 with two;
     // at 4 outstanding operations (bf16: one probe +1.3%, two in one group +3.4% over 2; fp32
     // one probe +3%), the fp32 two-probe perturb at 2 (4 measured equal or lower)
     constexpr int kPace2 = sizeof(typename S::storage) == 2 ? 4 : 2;
     const bool two_groups = w.two && w.a.group != w.b.group;
+    if constexpr (sizeof(typename S::storage) == 4) {
+      if (!w.two && sh.block == 128) {  // the streaming shape of one fp32 probe (shape_for)
+        go(perturb_kernel<S, false, N, 4, 128, 1>, w.a, 128);
+        return;
+      }
+    }
     const bool paced = (two_groups ? 2u : 1u) * (sizeof(typename S::storage) == 2 ? 2u : 1u) <= 2u;
     if (w.two)
       paced ? go(perturb_kernel<S, true, N, kPace2, kBlock, 1>, w.b) : go(perturb_kernel<S, true, N, 0, kBlock, 1>, w.b);
