@@ -5,6 +5,7 @@ sweeps' streaming loop with the probe work replaced by an XOR)."""
 import os
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -20,6 +21,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops off: no v_pk_{add,mul,fma}_f32 in the device code.
 DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+SWEEP_PARTS = 5  # zo_sweep.hip's ZO_PART: the entry points, and the kernels of four kinds of sweep
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math"]
 
 
@@ -38,17 +40,18 @@ def build(verbose=False):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         raise RuntimeError("no host C++ compiler found")
-    objs = []
+    objs, cmds = [], []
     for name in sorted(os.listdir(CSRC)):
         src = os.path.join(CSRC, name)
-        obj = os.path.join(BUILD, name + ".o")
         if name.endswith(".hip"):
-            _run([HIPCC, *DEVICE_FLAGS, "-I", INCLUDE, "-c", src, "-o", obj], verbose)
+            for part in range(SWEEP_PARTS):
+                objs.append(os.path.join(BUILD, f"{name}.{part}.o"))
+                cmds.append([HIPCC, *DEVICE_FLAGS, f"-DZO_PART={part}", "-I", INCLUDE, "-c", src, "-o", objs[-1]])
         elif name.endswith(".cpp"):
-            _run([cxx, *HOST_FLAGS, "-I", INCLUDE, "-c", src, "-o", obj], verbose)
-        else:
-            continue
-        objs.append(obj)
+            objs.append(os.path.join(BUILD, name + ".o"))
+            cmds.append([cxx, *HOST_FLAGS, "-I", INCLUDE, "-c", src, "-o", objs[-1]])
+    with ThreadPoolExecutor(SWEEP_PARTS) as pool:
+        list(pool.map(lambda cmd: _run(cmd, verbose), cmds))
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)

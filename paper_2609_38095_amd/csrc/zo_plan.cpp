@@ -125,17 +125,30 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 //     at four outstanding memory operations (+0.3 to 0.5% on three boxes; 2, 3, 5, 6 and 8,
 //     three groups in flight, 16-copy tables, 256 threads and one wave per stream all equal
 //     or slower);
-//   update, three bf16 groups: three workgroups per CU, one group ahead;
-//   update, four bf16 groups: 1024 threads, 32-copy tables in two planes (OPT-30B K = 32:
-//     21.9 -> 21.6 ms);
-//   update, eight bf16 groups (K = 57-64): 1024 threads sharing 16-copy tables in two planes
-//     (4 LDS cycles per 64-lane read instead of 6.3), four chunks per stream (OPT-1.3B K = 64:
-//     1.80 -> 1.57 ms; Qwen3-8B K = 60: 10.9 -> 9.9 ms);
-//   fp32 updates: one workgroup per CU up to three groups, two at four, three at five or six.
+//   update, three bf16 groups: 16-copy tables, two workgroups per CU (1.3 G weights: shared tables
+//     at three per CU, the count fixed at compile time, 870 -> 853 us);
+//   update, four bf16 groups: 512 threads, 16-copy tables in one plane, two workgroups per CU, one
+//     chunk per wave (a 3.75 G shard, K = 32: 2,769 -> 2,681 us against 1024 threads on 32-copy
+//     tables);
+//   update, five to eight bf16 groups: 1024 threads sharing 16-copy tables in two planes (4 LDS
+//     cycles per 64-lane read instead of 6.3), four chunks per stream (OPT-1.3B K = 64: 1.80 ->
+//     1.57 ms; Qwen3-8B K = 60: 10.9 -> 9.9 ms; 1.3 G weights, against shared tables, a run-time
+//     count and 4 KiB chunks: K = 40 1,410 -> 1,093 us, K = 48 1,572 -> 1,227, K = 56 1,744 ->
+//     1,374). 768 threads with one group ahead were 13% faster than 1024 on zero weights run
+//     back to back and 2.5% slower (1,590 against 1,550 us) on ordinary ones;
+//   update, nine to sixteen bf16 groups: the first eight groups as above, the others on shared
+//     tables behind them, 1024 threads up to twelve groups, else 768 (1.3 G weights: K = 72 2,343 ->
+//     2,019 us, K = 96 2,873 -> 2,259, K = 128 3,764 -> 3,414; K = 128 with 1024 threads spills
+//     registers: 3,599). Bound by VALU and the LDS together: 16-copy tables for all would need
+//     more than the LDS holds, shared tables for all take 6.3 LDS cycles a read (K = 96 with the
+//     count fixed: 2,630 us);
+//   fp32 updates: one workgroup per CU, 32-copy tables for one and two groups, shared ones for three
+//     (the count fixed at compile time: 2,607 -> 1,630 us); four: 16-copy tables, two workgroups per CU (K = 32: 1,697 -> 1,647 us); five to eight:
+//     512 threads sharing 16-copy tables (1.3 G weights: K = 40 1,911 -> 1,725 us, K = 48 2,128 ->
+//     1,836, K = 56 2,161 -> 2,001, K = 64 2,169 -> 2,069; 768 and 1024 threads spill registers).
 // An update with a restore probe inside its groups (Algorithm 1's schedule) is the plain
-// update with that group's table changed, and takes the update's shape. Other updates (five to
-// seven bf16 groups, more than eight, or more than six in fp32, and a restore probe outside
-// the update's groups) are bound by the generator or the LDS table lookups and keep 4 KiB
+// update with that group's table changed, and takes the update's shape. Other updates (more than
+// sixteen bf16 groups, or more than eight in fp32, and a restore probe outside the update's groups) are bound by the generator or the LDS table lookups and keep 4 KiB
 // chunks at full occupancy, as do perturbs smaller than the 256 MiB Infinity Cache (updates
 // of such buffers take 8 KiB chunks at full occupancy). Grids: up to
 // kDefaultMaxBlocks workgroups, grid-stride beyond (in-order dispatch of many short-lived
@@ -145,6 +158,10 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 // or two groups run one chunk per stream (OPT-13B: the perturb 6.48 -> 6.67 TB/s, OPT-30B
 // 6.20 -> 6.60; two probes in one group +1%, across two groups -0.3%, so those stay
 // grid-stride; 3 G fp32 weights: the two-probe perturb 6.30 -> 6.48 across two probe groups).
+// Four chunks per stream (each workgroup's table build serves four times the bytes) only where
+// they leave 512 workgroups, two rounds of the 256 CUs; one chunk per stream below, so that
+// buffers just above the cache still give every CU work (bf16, K = 64: 0.27 GB 287 -> 157 us, 0.4
+// GB 288 -> 236, while 1.07 GB takes 613 with four chunks and 623 with one).
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   const uint64_t group_bytes = kGroupElems * elem;
   const Shape short_chunks{static_cast<uint32_t>(4096 / group_bytes ? 4096 / group_bytes : 1), 0, 0};
@@ -170,10 +187,22 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   if (w.restore && !w.fold) return short_chunks;
   const uint32_t g = w.n_groups;
   Shape sh{chunk, 1, 0};
+  auto four_chunks = [&](uint32_t block) {
+    return elements * elem / (4 * kMaxChunkBytes * (block / 64)) >= 512;
+  };
   if (elem == 4) {
-    sh.blocks_per_cu = g <= 3 ? 1 : g == 4 ? 2 : g <= 6 ? 3 : 0;
-    if (sh.blocks_per_cu == 0) return short_chunks;
-    if (g <= 2) sh.copies = 32;  // one or two fp32 groups: 32-copy tables, one workgroup per CU
+    if (g <= 2) {  // 32-copy tables
+      sh.copies = 32;
+    } else if (g == 4) {
+      sh.copies = 16;
+      sh.blocks_per_cu = 2;
+    } else if (g >= 5 && g <= 8) {
+      sh.copies = 16;
+      sh.block = 512;
+      sh.chunks_per_wave = g == 8 && four_chunks(sh.block) ? 4 : 1;
+    } else if (g > 8) {
+      return short_chunks;
+    }
     return sh;
   }
   switch (g) {
@@ -187,19 +216,22 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
       sh.block = 512;
       return sh;
     case 3:
-      sh.blocks_per_cu = 3;
+      sh.copies = 16;
+      sh.blocks_per_cu = 2;
       return sh;
     case 4:
-      sh.block = 1024;
-      sh.copies = 32;
-      return sh;
-    case 8:
       sh.copies = 16;
-      sh.block = 1024;
-      sh.chunks_per_wave = 4;
+      sh.block = 512;
+      sh.blocks_per_cu = 2;
+      sh.chunks_per_wave = 1;
       return sh;
     default:
-      return short_chunks;
+      if (g > 16) return short_chunks;
+      sh.copies = g <= 8 ? 16 : 0;
+      sh.mixed = g > 8;
+      sh.block = g > 12 ? 768 : 1024;
+      sh.chunks_per_wave = four_chunks(sh.block) ? 4 : 1;
+      return sh;
   }
 }
 

@@ -103,6 +103,7 @@ struct Shape {
   uint32_t block = kBlock;   // threads per workgroup
   uint32_t wps = 1;          // waves per stream (per chunk)
   uint32_t copies = 0;       // update: copies of each table (0: one shared table)
+  bool mixed = false;        // update of more than eight groups: 16 copies of the first eight tables
 };
 
 // Whether global element 0 of a tensor stored from params with global offset `offset` would

@@ -40,6 +40,12 @@
 #include "zo_plan.h"
 #include "zo_stream.h"
 
+#ifdef ZO_PART
+#define ZO_HAS_PART(p) (ZO_PART == (p))
+#else
+#define ZO_HAS_PART(p) 1
+#endif
+
 namespace {
 
 using namespace zo;
@@ -212,11 +218,27 @@ template <int C>
 constexpr uint32_t groups_per_plane() {
   return C > 0 ? 64 / C : 1;
 }
+// A kernel of NG groups spreads the first 8 of them; from the ninth on a group has one shared
+// table, behind the spread ones (K = 72 to 128, see group_sums).
+constexpr int kSpreadGroups = 8;
+template <int NG, int C>
+constexpr uint32_t spread_groups() {
+  return C == 0 ? 0 : NG < kSpreadGroups ? NG : kSpreadGroups;
+}
+template <int NG, int C>
+constexpr uint32_t shared_base() {  // floats of the spread tables
+  return C == 0 ? 0 : (spread_groups<NG, C>() * C <= 64 ? 1 : 2) * kSpreadFloats;
+}
 // floats of the tables of NG groups: C interleaved copies, or one shared copy (C = 0)
 template <int NG, int C>
 constexpr uint32_t table_floats() {
-  static_assert(C == 0 || ((C == 16 || C == 32) && NG * C <= 128), "spread tables fill at most two planes");
-  return C == 0 ? NG * 256 : (NG * C <= 64 ? 1 : 2) * kSpreadFloats;
+  static_assert(C == 0 || ((C == 16 || C == 32) && spread_groups<NG, C>() * C <= 128),
+                "spread tables fill at most two planes");
+  return shared_base<NG, C>() + (NG - spread_groups<NG, C>()) * 256;
+}
+template <int NG, int C>
+__device__ __forceinline__ float* shared_table(float* tab, uint32_t g) {
+  return tab + shared_base<NG, C>() + 256u * (g - spread_groups<NG, C>());
 }
 
 // Build the n_groups x 256 table in LDS (C > 0: the interleaved copies). Entry (g, b):
@@ -230,7 +252,7 @@ constexpr uint32_t table_floats() {
 // and the coefficient reads are uniform (scalar loads), and the sign of slot s is an XOR of the
 // coefficient's sign bit with bit s of ~b. A workgroup of BLOCK threads builds BLOCK / 256
 // groups at a time: thread b + 256 m writes entry b of groups m, m + BLOCK / 256, ...
-template <int C, int BLOCK>
+template <int NG, int C, int BLOCK>
 __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32_t k_base, uint32_t K,
                                              uint32_t n_groups, float lr, uint32_t fold_g, const Probe& fold) {
   static_assert(BLOCK % 256 == 0, "one table entry per thread");
@@ -239,7 +261,7 @@ __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32
 #pragma unroll
   for (int s = 0; s < 8; ++s) flip[s] = ((~b) << (31 - s)) & 0x80000000u;
   const uint32_t g_first = k_base / 8;
-  for (uint32_t g = threadIdx.x >> 8; g < n_groups; g += BLOCK / 256) {
+  for (uint32_t g = threadIdx.x >> 8; g < (NG > 0 ? NG : n_groups); g += BLOCK / 256) {
     float v[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -249,17 +271,17 @@ __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32
     }
     float t = (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) * lr;
     if (g == fold_g) t = t - delta(fold, b);
-    if constexpr (C > 0) {
+    if (g < spread_groups<NG, C>()) {
       // entry b's C / 4 float4 of copies, 256 bytes after entry b - 1's: thread b writes them
       // starting at float4 b mod (C / 4), so that the lanes of each write spread over the banks
       // the group's copies occupy (in a fixed order all 64 would land on the same 4 banks)
-      constexpr uint32_t Q = C / 4, P = groups_per_plane<C>();
+      constexpr uint32_t Q = C > 0 ? C / 4 : 1, P = groups_per_plane<C>();
       float* e = tab + kSpreadFloats * (g / P) + 64u * b + C * (g % P);
       const float4 t4 = make_float4(t, t, t, t);
 #pragma unroll
       for (uint32_t q = 0; q < Q; ++q) *reinterpret_cast<float4*>(e + 4u * ((q + b) & (Q - 1))) = t4;
     } else {
-      tab[256u * g + b] = t;
+      shared_table<NG, C>(tab, g)[b] = t;
     }
   }
   __syncthreads();
@@ -282,12 +304,11 @@ __device__ __forceinline__ float spread_at(const float* tab, uint32_t lane_off, 
 // the group's generator words.
 template <class S, bool FIRST, int C>
 __device__ __forceinline__ void add_group(float (&acc)[GroupShape<S>::kRows][S::kVecElems], const float* tab,
-                                          const Gen& gen, uint64_t vbase, uint32_t lane, uint32_t g,
+                                          const float* tg, const Gen& gen, uint64_t vbase, uint32_t lane, uint32_t g,
                                           uint32_t g_first, uint32_t lane_off,
                                           uint32_t (&W)[GroupShape<S>::kRows][S::kWords]) {
   constexpr int R = GroupShape<S>::kRows;
   group_words(gen, vbase, lane, g_first + g, W, S());
-  const float* tg = tab + 256u * g;
 #pragma unroll
   for (int u = 0; u < R; ++u)
 #pragma unroll
@@ -301,28 +322,56 @@ __device__ __forceinline__ void add_group(float (&acc)[GroupShape<S>::kRows][S::
     }
 }
 
+// acc = fl(acc + p) with the rounding error of each sum gathered in comp (Neumaier).
+__device__ __forceinline__ void add_run(float& acc, float& comp, float p) {
+  const float a = acc, s = a + p;
+  comp += fabsf(a) >= fabsf(p) ? (a - s) + p : (p - s) + a;
+  acc = s;
+}
+
 // Sum of the tables of probe groups 0 .. n_groups-1 for the row group: NG > 0 fixes the count
-// at compile time (one run); NG == 0: runs of 8 groups, Neumaier-compensated across runs.
+// at compile time (one or two runs); NG == 0: runs of 8 groups, Neumaier-compensated across runs.
 template <class S, int NG, int C>
-__device__ __forceinline__ void group_sums(float (&acc)[GroupShape<S>::kRows][S::kVecElems], const float* tab,
+__device__ __forceinline__ void group_sums(float (&acc)[GroupShape<S>::kRows][S::kVecElems], float* tab,
                                            const Gen& gen, uint64_t vbase, uint32_t lane, uint32_t n_groups,
                                            uint32_t g_first, uint32_t lane_off) {
   constexpr int R = GroupShape<S>::kRows;
-  static_assert(C == 0 || NG > 0, "spread tables need a fixed group count");
+  static_assert(C == 0 || NG > 0, "spread tables need a bounded group count");
   uint32_t W[R][S::kWords];
+  // sum (+)= table tg of group g
+  auto first = [&](float (&sum)[R][S::kVecElems], auto c, uint32_t g, const float* tg) {
+    add_group<S, true, decltype(c)::value>(sum, tab, tg, gen, vbase, lane, g, g_first, lane_off, W);
+  };
+  auto next = [&](float (&sum)[R][S::kVecElems], auto c, uint32_t g, const float* tg) {
+    add_group<S, false, decltype(c)::value>(sum, tab, tg, gen, vbase, lane, g, g_first, lane_off, W);
+  };
+  using Spread = std::integral_constant<int, C>;
+  using Shared = std::integral_constant<int, 0>;
   if constexpr (NG > 0) {
-    add_group<S, true, C>(acc, tab, gen, vbase, lane, 0, g_first, lane_off, W);
+    constexpr int kRun = NG < 8 ? NG : 8;
+    first(acc, Spread{}, 0, tab);
 #pragma unroll
-    for (int g = 1; g < NG; ++g)
-      add_group<S, false, C>(acc, tab, gen, vbase, lane, g, g_first, lane_off, W);
+    for (int g = 1; g < kRun; ++g) next(acc, Spread{}, g, tab + 256 * g);
+    // The second run. Compensating a single sum changes nothing: fl(a + p) plus its own rounding
+    // error rounds to fl(a + p) again, so two runs are added plainly (9 VALU instructions per
+    // element fewer, the same bits).
+    if constexpr (NG > 8) {
+      float part[R][S::kVecElems];
+      first(part, Shared{}, 8, shared_table<NG, C>(tab, 8));
+#pragma unroll
+      for (int g = 9; g < NG; ++g) next(part, Shared{}, g, shared_table<NG, C>(tab, g));
+#pragma unroll
+      for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int e = 0; e < S::kVecElems; ++e) acc[u][e] = acc[u][e] + part[u][e];
+    }
   } else {
     float comp[R][S::kVecElems];
     for (uint32_t g0 = 0; g0 < n_groups; g0 += 8) {
       float part[R][S::kVecElems];
-      add_group<S, true, 0>(part, tab, gen, vbase, lane, g0, g_first, lane_off, W);
+      first(part, Shared{}, g0, tab + 256u * g0);
       const uint32_t g1 = n_groups - g0 < 8 ? n_groups : g0 + 8;
-      for (uint32_t g = g0 + 1; g < g1; ++g)
-        add_group<S, false, 0>(part, tab, gen, vbase, lane, g, g_first, lane_off, W);
+      for (uint32_t g = g0 + 1; g < g1; ++g) next(part, Shared{}, g, tab + 256u * g);
 #pragma unroll
       for (int u = 0; u < R; ++u)
 #pragma unroll
@@ -331,9 +380,7 @@ __device__ __forceinline__ void group_sums(float (&acc)[GroupShape<S>::kRows][S:
             acc[u][e] = part[u][e];
             comp[u][e] = 0.0f;
           } else {
-            const float a = acc[u][e], p = part[u][e], s = a + p;
-            comp[u][e] += fabsf(a) >= fabsf(p) ? (a - s) + p : (p - s) + a;
-            acc[u][e] = s;
+            add_run(acc[u][e], comp[u][e], part[u][e]);
           }
         }
     }
@@ -345,8 +392,8 @@ __device__ __forceinline__ void group_sums(float (&acc)[GroupShape<S>::kRows][S:
 }
 
 // Same sum for one tile on the element-wise path (one lane, all 16 elements).
-template <int C>
-__device__ __forceinline__ void tile_sums(float (&acc)[kTile], const float* tab, const Gen& gen, uint64_t t,
+template <int NG, int C>
+__device__ __forceinline__ void tile_sums(float (&acc)[kTile], float* tab, const Gen& gen, uint64_t t,
                                           uint32_t n_groups, uint32_t g_first) {
   float comp[kTile];
   for (uint32_t g0 = 0; g0 < n_groups; g0 += 8) {
@@ -359,11 +406,11 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], const float* tab,
       for (int j = 0; j < (int)kTile; ++j) {
         const uint32_t byte = word_byte(x[j >> 2], j & 3);
         float v;
-        if constexpr (C > 0) {
+        if (g < spread_groups<NG, C>()) {
           constexpr uint32_t P = groups_per_plane<C>();
-          v = tab[kSpreadFloats * (g / P) + 64u * byte + C * (g % P) + (threadIdx.x % C)];
+          v = tab[kSpreadFloats * (g / P) + 64u * byte + C * (g % P) + (threadIdx.x % (C > 0 ? C : 1))];
         } else {
-          v = tab[256u * g + byte];
+          v = shared_table<NG, C>(tab, g)[byte];
         }
         part[j] = g == g0 ? v : part[j] + v;
       }
@@ -374,9 +421,7 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], const float* tab,
         acc[j] = part[j];
         comp[j] = 0.0f;
       } else {
-        const float a = acc[j], p = part[j], s = a + p;
-        comp[j] += fabsf(a) >= fabsf(p) ? (a - s) + p : (p - s) + a;
-        acc[j] = s;
+        add_run(acc[j], comp[j], part[j]);
       }
     }
   }
@@ -391,8 +436,9 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], const float* tab,
 // is folded into that group's table (see build_tables), so the per-element work is the plain
 // update's; kPerElement, r lies outside them and is applied per element as t =
 // fl(theta + delta_r), then t minus the sum of the table values, its generator words made
-// after the group loop.
-enum RestoreMode { kNoRestore = 0, kFolded = 1, kPerElement = 2 };
+// after the group loop. kMaybeFolded: kFolded when r's weight is not zero, else kNoRestore, for
+// the group counts that keep one kernel for both.
+enum RestoreMode { kNoRestore = 0, kFolded = 1, kPerElement = 2, kMaybeFolded = 3 };
 
 template <class S, int NG, int RESTORE, int N, int C, int BLOCK, int WPS, int PACE = 0, int AHEAD = 0>
 __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uint32_t k_base, uint32_t K,
@@ -404,9 +450,10 @@ __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uin
   float* tab = NG > 0 ? tab_fix : tab_dyn;
   const uint32_t g_first = k_base / 8;
   // the table a folded restore changes (none: a group index no table has; below g_first wraps)
-  const uint32_t fold_g = RESTORE == kFolded ? r.group - g_first : 0xFFFFFFFFu;
+  const bool folds = RESTORE == kFolded || (RESTORE == kMaybeFolded && r.eps != 0.0f);
+  const uint32_t fold_g = folds ? r.group - g_first : 0xFFFFFFFFu;
   // the tables are built while each wave's first loads are in flight (for_each_group's prologue)
-  auto build = [&]() { build_tables<C, BLOCK>(tab, cf, k_base, K, n_groups, lr, fold_g, r); };
+  auto build = [&]() { build_tables<NG, C, BLOCK>(tab, cf, k_base, K, n_groups, lr, fold_g, r); };
   // the lane's copy of a spread table (byte 0) and the second plane's offset (byte 2)
   const uint32_t lane_off = 4u * (threadIdx.x % (C > 0 ? C : 32)) | (1u << 16);
   constexpr int R = GroupShape<S>::kRows;
@@ -432,7 +479,7 @@ __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uin
   }, build);
   for_each_edge<N, BLOCK>(ps, [&](const Plan& pl, uint64_t t) {
     float acc[kTile];
-    tile_sums<C>(acc, tab, gen, t, n_groups, g_first);
+    tile_sums<NG, C>(acc, tab, gen, t, n_groups, g_first);
     const uint4 rr = RESTORE == kPerElement ? gen_block(gen, t, r.group) : make_uint4(0, 0, 0, 0);
     const uint32_t xr[4] = {rr.x, rr.y, rr.z, rr.w};
     tile_elementwise<S>(reinterpret_cast<typename S::storage*>(pl.base), pl.lo, pl.hi, t, [&](int e, float v) {
@@ -454,8 +501,9 @@ __global__ __launch_bounds__(kBlock) void gen_bits_kernel(uint8_t* out, uint64_t
 
 // ---------------------------------------------------------------------------------------
 // Host side.
-int launch_status() { return hipGetLastError() == hipSuccess ? ZO_OK : ZO_ERR_HIP; }
+[[maybe_unused]] int launch_status() { return hipGetLastError() == hipSuccess ? ZO_OK : ZO_ERR_HIP; }
 
+#if ZO_HAS_PART(1) || ZO_HAS_PART(2) || ZO_HAS_PART(3) || ZO_HAS_PART(4)
 // A workgroup's LDS above 64 KiB (static plus dynamic) must be allowed per kernel before the
 // launch.
 template <class K>
@@ -471,6 +519,9 @@ template <int B, int W>
 struct Dims {
   static constexpr int block = B, wps = W;
 };
+
+template <int V>
+using Int = std::integral_constant<int, V>;
 
 template <class S, int N>
 void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
@@ -506,7 +557,6 @@ void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shap
       paced ? go(perturb_kernel<S, false, N, 4, kBlock, 1>, w.a) : go(perturb_kernel<S, false, N, 0, kBlock, 1>, w.a);
     return;
   }
-  const uint32_t copies = sh.copies;
   // One kernel: NG groups fixed at compile time (0: a runtime count, tables in dynamic LDS), C
   // copies of each table, launched with the dimensions it was built for.
   auto go = [&](auto kernel, auto groups, auto copies_c, auto dims) {
@@ -521,71 +571,98 @@ void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shap
     allow_lds(kernel, lds, static_lds);
     kernel<<<grid_of(B, W), dim3(B), lds, st>>>(ps, gen, w.k_base, w.K, w.n_groups, w.cf, w.lr, w.r);
   };
-  using std::integral_constant;
+  // Calls go for the kernel of NG groups, restore mode M, C copies of each table (of the first
+  // eight groups' tables from the ninth group on), B threads, W waves per stream.
+  auto launch = [&](auto groups, auto mode, auto copies_c, auto dims, auto pace, auto ahead) {
+    using D = decltype(dims);
+    go(update_kernel<S, decltype(groups)::value, static_cast<int>(decltype(mode)::value), N, decltype(copies_c)::value,
+                     D::block, D::wps, decltype(pace)::value, decltype(ahead)::value>,
+       groups, copies_c, dims);
+  };
   using D256 = Dims<kBlock, 1>;
-  using C0 = integral_constant<int, 0>;
+  const Int<0> c0{}, unpaced{}, one_or_two_ahead{};
+  const bool spread = sh.copies || sh.mixed;
   // a restore probe outside the update's groups: the per-element restore, runtime group count
   if (w.restore && !w.fold) {
-    go(update_kernel<S, 0, kPerElement, N, 0, kBlock, 1>, C0{}, C0{}, D256{});
+    launch(Int<0>{}, Int<kPerElement>{}, c0, D256{}, unpaced, one_or_two_ahead);
     return;
   }
   constexpr bool bf16 = sizeof(typename S::storage) == 2;
-  using G1 = integral_constant<int, 1>;
-  using G2 = integral_constant<int, 2>;
-  using G4 = integral_constant<int, 4>;
-  using G8 = integral_constant<int, 8>;
-  using C16 = integral_constant<int, 16>;
-  using C32 = integral_constant<int, 32>;
-  // The tables and launch dimensions shape_for picks for each group count: streaming bf16
-  // updates of two, four and eight groups take their own (two waves per stream; 1024-thread
-  // workgroups); everything else 256 threads. bf16 updates of one and two groups are paced at
-  // four outstanding memory operations, as the one-probe perturb. A
-  // folded restore runs the same code (its own instantiation, so that profiles tell the two
-  // calls apart).
+  // The tables and launch dimensions shape_for picks for each group count. bf16 updates of one and
+  // two groups are paced at four outstanding memory operations, as the one-probe perturb. With one,
+  // two, four and eight groups a folded restore runs the same code in an instantiation of its
+  // own, so that profiles tell the two calls apart.
   auto dispatch = [&](auto mode) {
-    constexpr int M = decltype(mode)::value;
     switch (w.n_groups) {
       case 1:
-        if (copies)
-          go(update_kernel<S, 1, M, N, 32, kBlock, 1>, G1{}, C32{}, D256{});
-        else
-          go(update_kernel<S, 1, M, N, 0, kBlock, 1, bf16 ? 4 : 0>, G1{}, C0{}, D256{});
-        break;
+        if constexpr (!bf16) {
+          if (spread) return launch(Int<1>{}, mode, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
+        }
+        return launch(Int<1>{}, mode, c0, D256{}, Int<bf16 ? 4 : 0>{}, one_or_two_ahead);
       case 2:
-        if (!copies)
-          go(update_kernel<S, 2, M, N, 0, kBlock, 1>, G2{}, C0{}, D256{});
-        else if constexpr (!bf16)
-          go(update_kernel<S, 2, M, N, 32, kBlock, 1>, G2{}, C32{}, D256{});
+        if (!spread) return launch(Int<2>{}, mode, c0, D256{}, unpaced, one_or_two_ahead);
+        if constexpr (bf16)
+          return launch(Int<2>{}, mode, Int<32>{}, Dims<512, 2>{}, Int<4>{}, one_or_two_ahead);
         else
-          go(update_kernel<S, 2, M, N, 32, 512, 2, 4>, G2{}, C32{}, Dims<512, 2>{});
-        break;
+          return launch(Int<2>{}, mode, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
       case 4:
-        if constexpr (bf16) {
-          if (copies) {
-            go(update_kernel<S, 4, M, N, 32, 1024, 1>, G4{}, C32{}, Dims<1024, 1>{});
-            break;
-          }
-        }
-        go(update_kernel<S, 4, M, N, 0, kBlock, 1>, G4{}, C0{}, D256{});
-        break;
-      case 8:
-        if constexpr (bf16) {
-          if (copies) {
-            go(update_kernel<S, 8, M, N, 16, 1024, 1>, G8{}, C16{}, Dims<1024, 1>{});
-            break;
-          }
-        }
-        go(update_kernel<S, 8, M, N, 0, kBlock, 1>, G8{}, C0{}, D256{});
-        break;
+        if (!spread) return launch(Int<4>{}, mode, c0, D256{}, unpaced, one_or_two_ahead);
+        if constexpr (bf16)
+          return launch(Int<4>{}, mode, Int<16>{}, Dims<512, 1>{}, unpaced, Int<2>{});
+        else
+          return launch(Int<4>{}, mode, Int<16>{}, D256{}, unpaced, Int<1>{});
       default:
-        go(update_kernel<S, 0, M, N, 0, kBlock, 1>, C0{}, C0{}, D256{});
-        break;
+        if (!spread) return launch(Int<8>{}, mode, c0, D256{}, unpaced, one_or_two_ahead);
+        return launch(Int<8>{}, mode, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
     }
   };
-  if (w.fold)
-    dispatch(integral_constant<int, kFolded>{});
-  else
-    dispatch(integral_constant<int, kNoRestore>{});
+  // three, five to seven and nine to sixteen groups (an odd count above eight runs with the next
+  // even one, its last table zero). A count fixed at compile time makes each table's offset an
+  // immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
+  // lets the compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU
+  // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
+  // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7.
+  auto other = [&](auto groups) {
+    constexpr int NG = decltype(groups)::value;
+    const Int<kMaybeFolded> mode{};
+    if (!spread) return launch(groups, mode, c0, D256{}, unpaced, Int<1>{});
+    if constexpr (NG == 3) {
+      if constexpr (bf16) launch(groups, mode, Int<16>{}, D256{}, unpaced, Int<2>{});
+    } else if constexpr (NG < 8) {
+      launch(groups, mode, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
+    } else if constexpr (bf16) {
+      launch(groups, mode, Int<16>{}, Dims<NG <= 12 ? 1024 : 768, 1>{}, unpaced, Int<1>{});
+    }
+  };
+  switch (w.n_groups) {
+    case 1:
+    case 2:
+    case 4:
+    case 8:
+      return w.fold ? dispatch(Int<kFolded>{}) : dispatch(Int<kNoRestore>{});
+    case 3:
+      return other(Int<3>{});
+    case 5:
+      return other(Int<5>{});
+    case 6:
+      return other(Int<6>{});
+    case 7:
+      return other(Int<7>{});
+    case 9:
+    case 10:
+      return other(Int<10>{});
+    case 11:
+    case 12:
+      return other(Int<12>{});
+    case 13:
+    case 14:
+      return other(Int<14>{});
+    case 15:
+    case 16:
+      return other(Int<16>{});
+    default:
+      return launch(Int<0>{}, Int<kMaybeFolded>{}, c0, D256{}, unpaced, one_or_two_ahead);
+  }
 }
 
 // One contiguous tensor.
@@ -602,17 +679,6 @@ int run_one(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t s
     launch_sweep<S>(ps, gen, w, sh, st);
     return launch_status();
   }, true);
-}
-
-int run_one_dt(void* params, zo_dtype dtype, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step,
-               const Sweep& w, void* stream) {
-  const int rc = check_params(params, dtype, offset, n);
-  if (rc != ZO_OK) return rc;
-  const int rs = check_sweep(w);
-  if (rs != ZO_OK) return rs;
-  if (n == 0) return ZO_OK;
-  return dtype == ZO_F32 ? run_one<F32>(params, offset, n, seed, step, w, stream)
-                         : run_one<BF16>(params, offset, n, seed, step, w, stream);
 }
 
 // A list of tensors (validated as a whole first), swept in launches of up to kSegsPerLaunch
@@ -637,14 +703,62 @@ int run_segments(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_
                                        }, true);
 }
 
+#endif  // a part with sweep kernels
+
+}  // namespace
+
+// The sweeps of one storage type over one tensor or a list, each a part of its own: the library
+// compiles this file once per part (ZO_PART 0 to 4; all at once when it is not defined), so that
+// the kernels of the four build in parallel.
+namespace zo {
+int sweep_flat_f32(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* st);
+int sweep_flat_bf16(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* st);
+int sweep_list_f32(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_t step, const Sweep& w, void* st);
+int sweep_list_bf16(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_t step, const Sweep& w, void* st);
+#if ZO_HAS_PART(1)
+int sweep_flat_f32(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* st) {
+  return run_one<F32>(params, offset, n, seed, step, w, st);
+}
+#endif
+#if ZO_HAS_PART(2)
+int sweep_flat_bf16(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* st) {
+  return run_one<BF16>(params, offset, n, seed, step, w, st);
+}
+#endif
+#if ZO_HAS_PART(3)
+int sweep_list_f32(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_t step, const Sweep& w, void* st) {
+  return run_segments<F32>(segs, n_segs, seed, step, w, st);
+}
+#endif
+#if ZO_HAS_PART(4)
+int sweep_list_bf16(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_t step, const Sweep& w, void* st) {
+  return run_segments<BF16>(segs, n_segs, seed, step, w, st);
+}
+#endif
+}  // namespace zo
+
+#if ZO_HAS_PART(0)
+namespace {
+
+int run_one_dt(void* params, zo_dtype dtype, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step,
+               const Sweep& w, void* stream) {
+  const int rc = check_params(params, dtype, offset, n);
+  if (rc != ZO_OK) return rc;
+  const int rs = check_sweep(w);
+  if (rs != ZO_OK) return rs;
+  if (n == 0) return ZO_OK;
+  return dtype == ZO_F32 ? sweep_flat_f32(params, offset, n, seed, step, w, stream)
+                         : sweep_flat_bf16(params, offset, n, seed, step, w, stream);
+}
+
 int run_segments_dt(const zo_segment* segs, uint32_t n_segs, zo_dtype dtype, uint64_t seed, uint32_t step,
                     const Sweep& w, void* stream) {
   const int rc = check_segments(segs, n_segs, dtype);
   if (rc != ZO_OK) return rc;
   const int rs = check_sweep(w);
   if (rs != ZO_OK) return rs;
-  return dtype == ZO_F32 ? run_segments<F32>(segs, n_segs, seed, step, w, stream)
-                         : run_segments<BF16>(segs, n_segs, seed, step, w, stream);
+  return dtype == ZO_F32 ? sweep_list_f32(segs, n_segs, seed, step, w, stream)
+                         : sweep_list_bf16(segs, n_segs, seed, step, w, stream);
 }
 
 }  // namespace
@@ -724,3 +838,4 @@ int zo_gen_bits(uint8_t* out_dev, uint64_t tile_begin, uint64_t n_tiles, uint64_
 void zo_set_max_blocks(uint32_t max_blocks) { set_max_blocks(max_blocks); }
 
 }  // extern "C"
+#endif  // ZO_HAS_PART(0)
