@@ -22,6 +22,7 @@ If libzo.so has not been built the import succeeds but every call raises ZoLibra
 there is no fallback implementation.
 """
 
+import array
 import ctypes
 import os
 
@@ -106,10 +107,11 @@ def _stream(theta_or_device, stream):
     library launches on the current device, so the tensors must live there."""
     import torch
     dev = theta_or_device.device if hasattr(theta_or_device, "device") else theta_or_device  # None: no tensors
-    if dev is not None and torch.device(dev).index not in (None, torch.cuda.current_device()):
+    if dev is not None and (dev if isinstance(dev, torch.device) else torch.device(dev)).index not in (None, torch.cuda.current_device()):
         raise ValueError(f"the tensors live on {dev}, the current device is cuda:{torch.cuda.current_device()}")
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+        index = torch.cuda.current_device()  # the tensors' device, checked above
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(index))  # no Stream object (1.5 us)
     if hasattr(stream, "cuda_stream"):
         sdev = getattr(stream, "device", None)
         if dev is not None and sdev is not None and torch.device(sdev) != torch.device(dev):
@@ -159,18 +161,35 @@ def _segments(tensors, offsets):
     tensors = list(tensors)
     if len(tensors) != len(offsets):
         raise ValueError("one global offset per tensor")
-    dts = {t.dtype for t in tensors}
-    if len(dts) > 1:
+    import torch
+    n = len(tensors)
+    flat = []
+    if n:
+        # one pass over the list (196 tensors: 48 us where an object and five checks with a set each
+        # took 160); anything it does not take is named by _check_segments
+        first = tensors[0]
+        dtype = getattr(first, "dtype", None)
+        dev = first.get_device() if isinstance(first, torch.Tensor) and first.is_cuda else -1
+        for t, o in zip(tensors, offsets):
+            if not (isinstance(t, torch.Tensor) and t.dtype == dtype and t.is_cuda and t.get_device() == dev
+                    and t.is_contiguous()):
+                _check_segments(tensors)
+            flat += (t.data_ptr(), int(o) & 0xFFFF_FFFF_FFFF_FFFF, t.numel())
+        if dtype not in (torch.float32, torch.bfloat16):
+            _check_segments(tensors)
+    arr = (ZoSegment * max(n, 1)).from_buffer(array.array("Q", flat or (0, 0, 0)))
+    dt = ZO_BF16 if n and dtype == torch.bfloat16 else ZO_F32
+    return arr, n, dt, (tensors[0] if tensors else None)
+
+
+def _check_segments(tensors):
+    """Raises what is wrong with a list of tensors."""
+    if len({t.dtype for t in tensors}) > 1:
         raise TypeError("all tensors must share one dtype")
-    devs = {t.device for t in tensors}
-    if len(devs) > 1:
+    if len({t.device for t in tensors}) > 1:
         raise ValueError("all tensors must be on one device (the stream's)")
-    arr = (ZoSegment * max(len(tensors), 1))()
-    dt = ZO_F32
-    for i, (t, o) in enumerate(zip(tensors, offsets)):
-        p, dt, n = _theta_args(t)
-        arr[i] = ZoSegment(p, int(o), n)
-    return arr, len(tensors), dt, (tensors[0] if tensors else None)
+    for t in tensors:
+        _theta_args(t)
 
 
 def zo_perturb_segments(tensors, offsets, k_a, eps_a, k_b, eps_b, seed, step, stream=None):
