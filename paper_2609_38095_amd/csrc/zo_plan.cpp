@@ -22,6 +22,12 @@ std::atomic<uint32_t> g_max_blocks{0};
 
 uint64_t ceil_div(uint64_t a, uint64_t b) { return a / b + (a % b != 0); }
 
+// 4 KiB chunks at full occupancy
+Shape short_chunks(size_t elem) {
+  const size_t group_bytes = kGroupElems * elem;
+  return Shape{static_cast<uint32_t>(4096 / group_bytes), 0, 0};
+}
+
 }  // namespace
 
 void set_max_blocks(uint32_t max_blocks) { g_max_blocks.store(max_blocks, std::memory_order_relaxed); }
@@ -164,9 +170,8 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 // GB 288 -> 236, while 1.07 GB takes 613 with four chunks and 623 with one).
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   const uint64_t group_bytes = kGroupElems * elem;
-  const Shape short_chunks{static_cast<uint32_t>(4096 / group_bytes ? 4096 / group_bytes : 1), 0, 0};
   if (elements * elem < kStreamBytes) {
-    if (!w.update) return short_chunks;
+    if (!w.update) return short_chunks(elem);
     // updates of cache-sized buffers: 8 KiB chunks, so that each workgroup's table build
     // serves twice the bytes (OPT-125M: K = 16 0.088 -> 0.084 ms, K = 60 0.201 -> 0.189 ms;
     // 16 and 32 KiB chunks measured slower at K = 16)
@@ -184,7 +189,7 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
     }
     return sh;
   }
-  if (w.restore && !w.fold) return short_chunks;
+  if (w.restore && !w.fold) return short_chunks(elem);
   const uint32_t g = w.n_groups;
   Shape sh{chunk, 1, 0};
   auto four_chunks = [&](uint32_t block) {
@@ -201,7 +206,7 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
       sh.block = 512;
       sh.chunks_per_wave = g == 8 && four_chunks(sh.block) ? 4 : 1;
     } else if (g > 8) {
-      return short_chunks;
+      return short_chunks(elem);
     }
     return sh;
   }
@@ -226,13 +231,35 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
       sh.chunks_per_wave = 1;
       return sh;
     default:
-      if (g > 16) return short_chunks;
+      if (g > 16) return short_chunks(elem);
       sh.copies = g <= 8 ? 16 : 0;
       sh.mixed = g > 8;
       sh.block = g > 12 ? 768 : 1024;
       sh.chunks_per_wave = four_chunks(sh.block) ? 4 : 1;
       return sh;
   }
+}
+
+// Shape of one launch of a list call. The call's weights decide whether it streams; its launches take
+// at most one chunk per stream: a tensor boundary then idles at most one chunk slot per stream of a
+// workgroup (Qwen3-8B as 399 tensors, K = 60: update 10.4-10.5 -> 9.8-9.9 ms against four chunks per
+// stream). Updates of five and more groups stream only where the launch's own tensors fill 256 MiB:
+// one of their workgroups takes up to 512 KiB of consecutive memory, so tensors of a few MiB leave
+// most of its waves idle and the chip half empty. A launch below runs as a cache-sized buffer, one
+// below 32 MiB in 4 KiB chunks, which still give every CU work. bf16, K = 96, a call of 300 MiB as 150
+// tensors (128 MiB a launch) 594 -> 381 us (417 in 4 KiB chunks), as 300 tensors 645 -> 428, as 600
+// (32 MiB) 1,230 -> 546 (539 in 4 KiB chunks), as 1,200 2,246 -> 690 (783 in 8 KiB chunks); fp32, K = 64,
+// 1.15 GB in launches of 117 MiB 700 -> 631. In launches of 267 to 384 MiB the two shapes lie within 14%
+// of each other either way; of 533 MiB (2.6 GB, bf16, K = 96) the streaming one takes 2,659 us, the
+// other 2,751.
+Shape list_shape(uint64_t call_elements, uint64_t launch_elements, size_t elem, const Sweep& w) {
+  const bool fixed_count = w.update && !(w.restore && !w.fold) && w.n_groups <= (elem == 2 ? 16u : 8u);
+  if (fixed_count && w.n_groups >= 5 && call_elements * elem >= kStreamBytes &&
+      launch_elements * elem < kStreamBytes)
+    return launch_elements * elem < kShortLaunchBytes ? short_chunks(elem) : shape_for(launch_elements, elem, w);
+  Shape sh = shape_for(call_elements, elem, w);
+  if (sh.chunks_per_wave > 1) sh.chunks_per_wave = 1;
+  return sh;
 }
 
 // Dynamic LDS that, with `static_lds` bytes of the kernel's own, admits exactly `cap`

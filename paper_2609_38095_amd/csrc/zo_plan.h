@@ -28,6 +28,7 @@ constexpr uint64_t kMaxLaunchEdges = 1ull << 31;   // edge tiles per launch, lik
 // storage lies); kernels that need aligned vectors plan without it.
 constexpr uint64_t kPieceElems = 1ull << 34;
 constexpr uint64_t kStreamBytes = 256ull << 20;    // sweeps at least this large stream (above the Infinity Cache)
+constexpr uint64_t kShortLaunchBytes = 32ull << 20;  // launches of a list call below this take 4 KiB chunks (list_shape)
 
 // One segment: global elements [lo, hi) stored from `base` (the address of global element lo).
 // The `span` full row groups from global group g_lo (stored from `gbase`) take the vector
@@ -125,6 +126,7 @@ Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t 
 uint32_t plan_chunks(const Plan& pl, uint32_t chunk_groups);
 uint32_t grid_for(uint64_t work_items, uint64_t per_block, uint32_t block, bool sized = false);
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w);
+Shape list_shape(uint64_t call_elements, uint64_t launch_elements, size_t elem, const Sweep& w);
 size_t occupancy_lds(uint32_t cap, size_t static_lds);
 void set_max_blocks(uint32_t max_blocks);
 
@@ -199,6 +201,26 @@ int plan_segments(const zo_segment* segs, uint32_t n_segs, size_t elem, uint32_t
     }
   }
   return ps.count ? launch(ps) : ZO_OK;
+}
+
+// A list call: the list in batches of up to N non-empty segments, each planned by plan_segments
+// in the shape list_shape picks for it. Calls launch(plans, shape).
+template <int N, class Launch>
+int plan_list(const zo_segment* segs, uint32_t n_segs, size_t elem, const Sweep& w, Launch launch) {
+  uint64_t total = 0;
+  for (uint32_t i = 0; i < n_segs; ++i) total += segs[i].n;
+  for (uint32_t i = 0, j = 0; i < n_segs; i = j) {
+    uint64_t batch = 0;
+    for (int filled = 0; j < n_segs && filled < N; ++j) {
+      batch += segs[j].n;
+      filled += segs[j].n != 0;
+    }
+    const Shape sh = list_shape(total, batch, elem, w);
+    const int rc = plan_segments<N>(segs + i, j - i, elem, sh.chunk_groups, streams_per_block(sh),
+                                    [&](const Plans<N>& ps) { return launch(ps, sh); }, true);
+    if (rc != ZO_OK) return rc;
+  }
+  return ZO_OK;
 }
 
 }  // namespace zo

@@ -692,19 +692,12 @@ int run_segments(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_
                  void* stream) {
   const Gen gen = make_gen(seed, step);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  uint64_t total = 0;  // the call's weights decide the streaming shape of all its launches
-  for (uint32_t i = 0; i < n_segs; ++i) total += segs[i].n;
-  Shape sh = shape_for(total, sizeof(typename S::storage), w);
-  // at most one chunk per stream: a tensor boundary then idles at most one chunk slot per
-  // stream of a workgroup (Qwen3-8B as 399 tensors, K = 60: update 10.4-10.5 -> 9.8-9.9 ms
-  // against four chunks per stream)
-  if (sh.chunks_per_wave > 1) sh.chunks_per_wave = 1;
   (void)hipGetLastError();
-  return plan_segments<kSegsPerLaunch>(segs, n_segs, sizeof(typename S::storage), sh.chunk_groups,
-                                       streams_per_block(sh), [&](const Plans<kSegsPerLaunch>& ps) {
-                                         launch_sweep<S>(ps, gen, w, sh, st);
-                                         return launch_status();
-                                       }, true);
+  return plan_list<kSegsPerLaunch>(segs, n_segs, sizeof(typename S::storage), w,
+                                   [&](const Plans<kSegsPerLaunch>& ps, const Shape& sh) {
+                                     launch_sweep<S>(ps, gen, w, sh, st);
+                                     return launch_status();
+                                   });
 }
 
 #endif  // a part with sweep kernels

@@ -1,0 +1,76 @@
+// Launch shapes of flat and list calls, on the CPU.
+#include <cstdio>
+#include <vector>
+
+#include "zo_plan.h"
+
+using namespace zo;
+
+static int failed = 0;
+#define CHECK(cond, ...)                                             \
+  do {                                                               \
+    if (!(cond)) {                                                   \
+      std::fprintf(stderr, "line %d: %s: ", __LINE__, #cond);        \
+      std::fprintf(stderr, __VA_ARGS__);                             \
+      std::fprintf(stderr, "\n");                                    \
+      ++failed;                                                      \
+    }                                                                \
+  } while (0)
+
+static Sweep update_of(uint32_t groups) {
+  static const std::vector<float> c(ZO_K_MAX, 0.5f);
+  Sweep w{};
+  if (make_update_sweep(w, 0, 8 * groups, c.data(), 1e-3f, nullptr) != ZO_OK || w.n_groups != groups) ++failed;
+  return w;
+}
+
+// A list of `tensors` equal tensors of `bytes` each, 512-byte aligned, with an empty one after every seventh.
+static std::vector<zo_segment> list_of(uint32_t tensors, uint64_t bytes, size_t elem) {
+  std::vector<zo_segment> segs;
+  const uint64_t stride = (bytes + 511) / 512 * 512;
+  for (uint32_t i = 0; i < tensors; ++i) {
+    segs.push_back({reinterpret_cast<void*>(0x7f0000000000ull + i * stride), i * (bytes / elem), bytes / elem});
+    if (i % 7 == 6) segs.push_back({nullptr, 0, 0});
+  }
+  return segs;
+}
+
+// Every launch of a list call that streams as a whole: updates of five and more groups take workgroups of
+// more than 256 threads only where the launch's own tensors are 256 MiB and more; every tensor is planned
+// once, in order.
+static void check_lists() {
+  for (size_t elem : {(size_t)2, (size_t)4})
+    for (uint32_t groups = 1; groups <= 17; ++groups)
+      for (uint32_t tensors : {1u, 40u, 64u, 65u, 150u, 300u, 1200u, 12000u})
+        for (uint64_t total : {300ull << 20, 1100ull << 20, 40000ull << 20}) {
+          const std::vector<zo_segment> segs = list_of(tensors, total / tensors / elem * elem, elem);
+          const Sweep w = update_of(groups);
+          uint32_t planned = 0;
+          const int rc = plan_list<kSegsPerLaunch>(segs.data(), static_cast<uint32_t>(segs.size()), elem, w,
+                                                   [&](const Plans<kSegsPerLaunch>& ps, const Shape& sh) {
+            uint64_t bytes = 0;
+            for (uint32_t s = 0; s < ps.count; ++s, ++planned) {
+              bytes += (ps.p[s].hi - ps.p[s].lo) * elem;
+              CHECK(reinterpret_cast<uintptr_t>(ps.p[s].base) == 0x7f0000000000ull + planned * ((total / tensors / elem * elem + 511) / 512 * 512),
+                    "tensor %u", planned);
+            }
+            CHECK(ps.chunk_groups == sh.chunk_groups, "chunks of another shape");
+            CHECK(sh.chunks_per_wave <= 1, "%u chunks per stream", sh.chunks_per_wave);
+            if (groups >= 5 && bytes < kStreamBytes)
+              CHECK(sh.block == kBlock && sh.copies == 0 && !sh.mixed,
+                    "elem %zu, %u groups, a launch of %llu MiB in workgroups of %u threads", elem, groups,
+                    (unsigned long long)(bytes >> 20), sh.block);
+            if (groups >= 5 && bytes < kShortLaunchBytes) CHECK(sh.chunk_groups * kGroupElems * elem == 4096, "chunks");
+            const bool fixed = groups <= (elem == 2 ? 16u : 8u);
+            if (groups >= 5 && fixed && bytes >= kStreamBytes) CHECK(sh.block > kBlock, "%u groups", groups);
+            return static_cast<int>(ZO_OK);
+          });
+          CHECK(rc == ZO_OK && planned == tensors, "%u of %u tensors", planned, tensors);
+        }
+}
+
+int main() {
+  check_lists();
+  if (!failed) std::printf("ok\n");
+  return failed != 0;
+}
