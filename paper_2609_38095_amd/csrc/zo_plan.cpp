@@ -164,10 +164,14 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 // or two groups run one chunk per stream (OPT-13B: the perturb 6.48 -> 6.67 TB/s, OPT-30B
 // 6.20 -> 6.60; two probes in one group +1%, across two groups -0.3%, so those stay
 // grid-stride; 3 G fp32 weights: the two-probe perturb 6.30 -> 6.48 across two probe groups).
-// Four chunks per stream (each workgroup's table build serves four times the bytes) only where
-// they leave 512 workgroups, two rounds of the 256 CUs; one chunk per stream below, so that
-// buffers just above the cache still give every CU work (bf16, K = 64: 0.27 GB 287 -> 157 us, 0.4
-// GB 288 -> 236, while 1.07 GB takes 613 with four chunks and 623 with one).
+// Four chunks per stream (each workgroup's table build serves four times the bytes) where they take no
+// longer, counted in rounds of one workgroup on each of the 256 CUs: a round of four chunks lasts as
+// long as four rounds of one, less the table builds (2% of it in bf16, 10% in fp32, measured where both
+// fill their last round), and one started for a few last workgroups lasts as long as a full one. bf16, four
+// chunks against one: eight groups at 0.94 GB (2 rounds for 8) 578 against 601 us, at 1.08 GB (3 for 9)
+// 900 against 700, at 2.63 GB (5 for 20) 1,526 against 1,578; sixteen groups at 0.82 GB (3 for 9) 1,462
+// against 1,146. fp32, eight groups, at 0.54 GB (3 for 9) 280 against 242, at 1.78 GB (7 for 27) 713
+// against 765.
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   const uint64_t group_bytes = kGroupElems * elem;
   if (elements * elem < kStreamBytes) {
@@ -193,7 +197,10 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   const uint32_t g = w.n_groups;
   Shape sh{chunk, 1, 0};
   auto four_chunks = [&](uint32_t block) {
-    return elements * elem / (4 * kMaxChunkBytes * (block / 64)) >= 512;
+    auto rounds = [&](uint64_t chunks) {  // memory may cut one workgroup's block off the first
+      return ceil_div(elements * elem / (chunks * kMaxChunkBytes * (block / 64)) + 1, kCUs);
+    };
+    return 400 * rounds(4) <= (elem == 2 ? 102 : 110) * rounds(1);
   };
   if (elem == 4) {
     if (g <= 2) {  // 32-copy tables

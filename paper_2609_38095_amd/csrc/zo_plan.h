@@ -18,6 +18,7 @@ constexpr uint32_t kBlock = 256;            // threads per workgroup of the defa
 constexpr uint64_t kGroupElems = 1024;      // elements per row group (one Philox block per lane)
 constexpr uint64_t kMaxChunkBytes = 32768;  // bytes a wave streams per chunk, at most
 constexpr uint32_t kDefaultMaxBlocks = 65536;
+constexpr uint32_t kCUs = 256;
 constexpr uint32_t kSegsPerLaunch = 64;            // segments per batched launch (kernel arguments, ~5 KiB)
 constexpr uint64_t kMaxLaunchChunks = 1ull << 31;  // chunks per launch: 32-bit indices with room for the stride
 constexpr uint64_t kMaxLaunchEdges = 1ull << 31;   // edge tiles per launch, likewise
