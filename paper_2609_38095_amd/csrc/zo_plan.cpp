@@ -62,11 +62,24 @@ bool groups_aligned(const void* params, uint64_t offset, size_t elem) {
   return ((reinterpret_cast<uintptr_t>(params) - static_cast<uintptr_t>(offset * elem)) & 15u) == 0;
 }
 
+// From how many weights of a launch on its misaligned tensors (groups_aligned false) take full row
+// groups. Smaller launches are bound by the latency of one wave: a tile per lane and nothing after it
+// is shorter than a chunk of row groups followed by the head and tail tiles, the more so the more
+// probe groups; larger ones by the element-wise path's 2-byte or 4-byte accesses. Flat calls at an odd
+// address, element-wise against row groups, us: bf16, one group, 0.9 M weights 7.8 / 7.8, 1.3 M 9.9 / 8.8;
+// 8 groups, 40 thousand 12.3 / 19.5, 2.6 M 19.3 / 20.7, 3.6 M 22.5 / 20.7; 17 groups, 40 thousand 20.6 /
+// 40.3, 3.6 M 32.9 / 41.5, 5.1 M 47.7 / 44.2; fp32, one probe, 240 thousand 6.7 / 6.4; 8 groups, 0.9 M 14.0 /
+// 16.3, 1.3 M 19.3 / 17.1; 24 groups, 2.6 M 41.0 / 48.2, 5.1 M 68.0 / 50.5.
+uint64_t any_alignment_from(size_t elem, const Sweep& w) {
+  const uint64_t groups = w.update ? w.n_groups : 1;
+  if (elem == 2) return (3 + std::min<uint64_t>(groups, 17)) << 18;
+  return groups <= 2 ? 1ull << 18 : groups <= 16 ? 1ull << 20 : 1ull << 22;
+}
+
 // The addresses are device addresses: they are only ever offset here, never dereferenced, and
-// are carried as integers until the plan holds them. Full row groups sit at
-// any weight's address with any_alignment; without it misaligned storage has none, and n must then
-// be at most kPieceElems (plan_segments splits larger tensors), so that the edge-tile counts fit
-// 32 bits.
+// are carried as integers until the plan holds them. Full row groups sit at any weight's address;
+// without any_alignment misaligned storage has none, and n must be below 2^34, so that the edge-tile
+// counts fit 32 bits.
 Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t chunk_groups, bool any_alignment) {
   Plan pl{};
   pl.base = static_cast<char*>(params);

@@ -21,13 +21,6 @@ constexpr uint32_t kDefaultMaxBlocks = 65536;
 constexpr uint32_t kCUs = 256;
 constexpr uint32_t kSegsPerLaunch = 64;            // segments per batched launch (kernel arguments, ~5 KiB)
 constexpr uint64_t kMaxLaunchChunks = 1ull << 31;  // chunks per launch: 32-bit indices with room for the stride
-constexpr uint64_t kMaxLaunchEdges = 1ull << 31;   // edge tiles per launch, likewise
-// Planned without any_alignment, storage that is not 16-byte aligned relative to the global
-// index has no full row groups: every element takes the element-wise path, one tile per lane,
-// and the tensor is planned in pieces of at most kPieceElems elements (2^30 tiles), so that
-// edge-tile counts stay 32-bit. The sweeps plan with any_alignment (full row groups wherever the
-// storage lies); kernels that need aligned vectors plan without it.
-constexpr uint64_t kPieceElems = 1ull << 34;
 constexpr uint64_t kStreamBytes = 256ull << 20;    // sweeps at least this large stream (above the Infinity Cache)
 constexpr uint64_t kShortLaunchBytes = 32ull << 20;  // launches of a list call below this take 4 KiB chunks (list_shape)
 
@@ -42,7 +35,8 @@ constexpr uint64_t kShortLaunchBytes = 32ull << 20;  // launches of a list call 
 // workgroup streams one aligned block of memory (OPT-13B bf16 perturb: 7.65 ms with the
 // workgroups' 128 KiB blocks aligned, 8.0-8.25 ms shifted by one to three 32 KiB chunks). The
 // edge tiles [head_t0, +head_nt) and [tail_t0, +tail_nt) (fewer than 1024 elements at each
-// end) take the element-wise path. The kernels walk chunks and groups with
+// end; all of a misaligned tensor in a small launch, see any_alignment_from) take the element-wise
+// path. The kernels walk chunks and groups with
 // 32-bit indices relative to the segment (compares of 64-bit indices need a vector register
 // on gfx950, and writing one that a pending store still reads makes the wave wait for that
 // store); a segment stays below 2^30 row groups (n < ZO_N_MAX) and a launch below 2^31 chunks.
@@ -122,8 +116,9 @@ Probe make_probe(uint32_t k, float eps);
 Gen make_gen(uint64_t seed, uint32_t step);
 
 // Planning.
+uint64_t any_alignment_from(size_t elem, const Sweep& w);
 Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t chunk_groups,
-               bool any_alignment = false);
+               bool any_alignment = true);
 uint32_t plan_chunks(const Plan& pl, uint32_t chunk_groups);
 uint32_t grid_for(uint64_t work_items, uint64_t per_block, uint32_t block, bool sized = false);
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w);
@@ -164,22 +159,24 @@ uint32_t plans_grid(const Plans<N>& ps, const Shape& sh) {
 }
 
 // A list of tensors in launches of up to N plans: calls launch(plans) for every batch.
-// Segments with n = 0 are skipped; without any_alignment, a segment that is not 16-byte aligned
-// is planned in pieces of kPieceElems; a batch is closed before its chunk or edge-tile count would reach 2^31.
+// Segments with n = 0 are skipped; a batch is closed before its chunk count would reach 2^31.
 // `streams`: the streams of one workgroup of the launches (the chunk alignment of add_plan).
+// any_alignment: as in make_plan; only a list of fewer than 2^34 elements may be planned without.
 // Returns the first status launch() returns other than ZO_OK, else ZO_OK. The list must have
 // passed check_segments.
 template <int N, class Launch>
 int plan_segments(const zo_segment* segs, uint32_t n_segs, size_t elem, uint32_t chunk_groups, uint32_t streams,
-                  Launch launch, bool any_alignment = false) {
+                  Launch launch, bool any_alignment = true) {
   Plans<N> ps{};
   ps.chunk_groups = chunk_groups;
-  auto add = [&](const Plan& pl) {
+  for (uint32_t i = 0; i < n_segs; ++i) {
+    const zo_segment& sg = segs[i];
+    if (sg.n == 0) continue;
+    const Plan pl = make_plan(sg.params, sg.offset, sg.n, elem, chunk_groups, any_alignment);
     // the plan's chunks plus up to streams - 1 alignment slots
-    if (ps.count && (ps.chunk_end[ps.count - 1] + static_cast<uint64_t>(plan_chunks(pl, chunk_groups)) + streams >=
-                         kMaxLaunchChunks ||
-                     ps.edge_end[ps.count - 1] + static_cast<uint64_t>(pl.head_nt) + pl.tail_nt >= kMaxLaunchEdges)) {
-      const int rc = launch(ps);  // keep a launch's chunk and edge counts 32-bit
+    if (ps.count && ps.chunk_end[ps.count - 1] + static_cast<uint64_t>(plan_chunks(pl, chunk_groups)) + streams >=
+                        kMaxLaunchChunks) {
+      const int rc = launch(ps);  // keep a launch's chunk count 32-bit
       if (rc != ZO_OK) return rc;
       ps.count = 0;
     }
@@ -188,17 +185,6 @@ int plan_segments(const zo_segment* segs, uint32_t n_segs, size_t elem, uint32_t
       const int rc = launch(ps);
       if (rc != ZO_OK) return rc;
       ps.count = 0;
-    }
-    return static_cast<int>(ZO_OK);
-  };
-  for (uint32_t i = 0; i < n_segs; ++i) {
-    const zo_segment& sg = segs[i];
-    const uint64_t piece = any_alignment || groups_aligned(sg.params, sg.offset, elem) ? sg.n : kPieceElems;
-    for (uint64_t done = 0; done < sg.n; done += piece) {
-      const uint64_t m = sg.n - done < piece ? sg.n - done : piece;
-      void* at = reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(sg.params) + static_cast<uintptr_t>(done * elem));
-      const int rc = add(make_plan(at, sg.offset + done, m, elem, chunk_groups, any_alignment));
-      if (rc != ZO_OK) return rc;
     }
   }
   return ps.count ? launch(ps) : ZO_OK;
@@ -218,7 +204,8 @@ int plan_list(const zo_segment* segs, uint32_t n_segs, size_t elem, const Sweep&
     }
     const Shape sh = list_shape(total, batch, elem, w);
     const int rc = plan_segments<N>(segs + i, j - i, elem, sh.chunk_groups, streams_per_block(sh),
-                                    [&](const Plans<N>& ps) { return launch(ps, sh); }, true);
+                                    [&](const Plans<N>& ps) { return launch(ps, sh); },
+                                    batch >= any_alignment_from(elem, w));
     if (rc != ZO_OK) return rc;
   }
   return ZO_OK;

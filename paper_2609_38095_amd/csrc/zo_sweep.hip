@@ -677,12 +677,11 @@ int run_one(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t s
   hipStream_t st = static_cast<hipStream_t>(stream);
   const zo_segment seg{params, offset, n};
   (void)hipGetLastError();
-  // one launch, full row groups at any alignment
   return plan_segments<1>(&seg, 1, sizeof(typename S::storage), sh.chunk_groups, streams_per_block(sh),
                           [&](const Plans<1>& ps) {
     launch_sweep<S>(ps, gen, w, sh, st);
     return launch_status();
-  }, true);
+  }, n >= any_alignment_from(sizeof(typename S::storage), w));
 }
 
 // A list of tensors (validated as a whole first), swept in launches of up to kSegsPerLaunch

@@ -1,6 +1,6 @@
 // Plans of tensors stored at any weight's address (any_alignment), on the CPU: the head tiles,
 // full row groups and tail tiles partition [offset, offset + n), every row group's bytes lie
-// inside the tensor, and wherever the default planning has full row groups the plans agree.
+// inside the tensor, and wherever planning without any_alignment has full row groups the plans agree.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -59,7 +59,7 @@ int main() {
             if (groups_aligned(seg.params, off, elem)) {
               Plans<1> def{};
               def.chunk_groups = cg;
-              add_plan(def, make_plan(seg.params, off, n, elem, cg), elem, 4);
+              add_plan(def, make_plan(seg.params, off, n, elem, cg, false), elem, 4);
               CHECK(std::memcmp(&def, &ps, sizeof def) == 0);
             }
             return static_cast<int>(ZO_OK);

@@ -96,8 +96,40 @@ static void check_rounds() {
     }
 }
 
+// Misaligned tensors: element by element in small launches, on row groups in larger ones; aligned ones
+// always on row groups; and the line rises with the probe groups.
+static void check_misaligned() {
+  for (size_t elem : {(size_t)2, (size_t)4}) {
+    uint64_t last = 0;
+    for (uint32_t groups : {1u, 2u, 3u, 4u, 8u, 16u, 17u, 40u, 128u}) {
+      const Sweep w = update_of(groups);
+      const uint64_t from = any_alignment_from(elem, w);
+      CHECK(from >= last && from <= 1ull << 23, "%u groups from %llu weights", groups, (unsigned long long)from);
+      last = from;
+      for (uint32_t tensors : {1u, 10u, 64u, 200u})
+        for (uint64_t weights : {from / 2, from - 1, from, 4 * from}) {
+          std::vector<zo_segment> segs;
+          for (uint32_t i = 0; i < tensors; ++i)  // every other tensor misaligned
+            segs.push_back({reinterpret_cast<void*>(0x7f0000000000ull + i * (weights * elem + 4096) + (i % 2) * elem), 0,
+                            weights / tensors + (i == 0 ? weights % tensors : 0)});
+          plan_list<kSegsPerLaunch>(segs.data(), tensors, elem, w, [&](const Plans<kSegsPerLaunch>& ps, const Shape&) {
+            uint64_t n = 0;
+            for (uint32_t s = 0; s < ps.count; ++s) n += ps.p[s].hi - ps.p[s].lo;
+            for (uint32_t s = 0; s < ps.count; ++s) {
+              const bool aligned = groups_aligned(ps.p[s].base, 0, elem), fits = ps.p[s].hi >= kGroupElems;
+              CHECK((ps.p[s].span != 0) == (fits && (aligned || n >= from)), "elem %zu, %u groups, %llu weights in %u tensors: %s tensor on %u row groups",
+                    elem, groups, (unsigned long long)n, ps.count, aligned ? "aligned" : "misaligned", ps.p[s].span);
+            }
+            return static_cast<int>(ZO_OK);
+          });
+        }
+    }
+  }
+}
+
 int main() {
   check_lists();
+  check_misaligned();
   check_rounds();
   if (!failed) std::printf("ok\n");
   return failed != 0;

@@ -3,8 +3,9 @@
 // CPU the index arithmetic the sweep kernels do with what the planner hands them, and checks
 // that every element of every tensor is covered exactly once:
 //   - make_plan: head tiles, full row groups and tail tiles partition [offset, offset + n),
-//     for element sizes 2 and 4, aligned and unaligned bases, offsets up to the top of the
-//     64-bit index range and n up to ZO_N_MAX - 1;
+//     for element sizes 2 and 4, bases at any element's address, offsets up to the top of the
+//     64-bit index range and n up to ZO_N_MAX - 1, and (n below 2^34) without row groups on
+//     misaligned bases;
 //   - the chunk walk of the kernels (32-bit chunk and group indices relative to a segment,
 //     one to four waves per stream) covers the full row groups exactly once;
 //   - plan_segments: batches of at most 64 segments, each below 2^31 chunks, every
@@ -131,14 +132,14 @@ static void check_alignment(const Plans<N>& ps, size_t elem, uint32_t streams, c
 }
 
 // make_plan's split of [offset, offset + n) into edge tiles and full row groups.
-static void check_plan(uintptr_t addr, uint64_t offset, uint64_t n, size_t elem, uint32_t cg) {
+static void check_plan(uintptr_t addr, uint64_t offset, uint64_t n, size_t elem, uint32_t cg, bool any = true) {
   char what[160];
   std::snprintf(what, sizeof what, "plan(addr=%#llx, offset=%llu, n=%llu, elem=%zu, cg=%u)",
                 (unsigned long long)addr, (unsigned long long)offset, (unsigned long long)n, elem, cg);
-  const Plan pl = make_plan(reinterpret_cast<void*>(addr), offset, n, elem, cg);
+  const Plan pl = make_plan(reinterpret_cast<void*>(addr), offset, n, elem, cg, any);
   const u128 lo = offset, hi = (u128)offset + n;
   CHECK(pl.lo == offset && (u128)pl.hi == hi, "%s: range", what);
-  const bool aligned = ((addr - (uintptr_t)(offset * elem)) & 15u) == 0;
+  const bool aligned = any || ((addr - (uintptr_t)(offset * elem)) & 15u) == 0;
   u128 head_end = hi, tail_begin = hi;
   if (pl.span) {
     CHECK(aligned, "%s: full groups on a misaligned base", what);
@@ -148,7 +149,9 @@ static void check_plan(uintptr_t addr, uint64_t offset, uint64_t n, size_t elem,
     const uintptr_t gb = reinterpret_cast<uintptr_t>(pl.gbase);
     CHECK(pl.head == gb / (kGroupElems * elem) % cg, "%s: head", what);
     CHECK(gb == addr + (uintptr_t)((f0 - lo) * elem), "%s: gbase", what);
-    CHECK((gb & 15u) == 0, "%s: gbase misaligned", what);
+    CHECK(any || (gb & 15u) == 0, "%s: gbase misaligned", what);
+    CHECK((u128)gb + (u128)pl.span * kGroupElems * elem <= (u128)addr + (u128)n * elem && gb >= addr,
+          "%s: row groups outside the tensor", what);
     head_end = f0;
     tail_begin = f1;
   } else if (aligned) {
@@ -171,42 +174,32 @@ static void check_plan(uintptr_t addr, uint64_t offset, uint64_t n, size_t elem,
   } else {
     CHECK(pl.tail_nt == 0, "%s: tail tiles without a tail", what);
   }
-  if (aligned)  // storage misaligned relative to the global index takes the element path throughout
+  if (aligned)  // else the element path throughout
     CHECK((u128)pl.head_nt * kTile <= 2 * kGroupElems + kTile && (u128)pl.tail_nt * kTile <= kGroupElems + kTile,
           "%s: edge paths longer than a row group", what);
   for (uint32_t wps : {1u, 2u, 4u}) check_chunk_walk(pl, cg, wps, what);
+  if (any && n < (1ull << 34)) check_plan(addr, offset, n, elem, cg, false);
 }
 
-// A tensor through plan_segments (one plan per launch, as zo_perturb launches one tensor):
-// the plans' element ranges, in order, partition [offset, offset + n), each plan as check_plan
-// requires, and every launch stays below 2^31 edge tiles.
-static void check_pieces(uintptr_t addr, uint64_t offset, uint64_t n, size_t elem, uint32_t cg,
-                         uint32_t streams = 4) {
+// A tensor through plan_segments (as zo_perturb launches one tensor): one launch of one plan, as
+// check_plan requires.
+static void check_one(uintptr_t addr, uint64_t offset, uint64_t n, size_t elem, uint32_t cg, uint32_t streams = 4) {
   const zo_segment seg{reinterpret_cast<void*>(addr), offset, n};
-  u128 next = offset;
   size_t plans = 0;
   const int rc = plan_segments<1>(&seg, 1, elem, cg, streams, [&](const Plans<1>& ps) {
     const Plan& pl = ps.p[0];
-    check_alignment(ps, elem, streams, "pieces");
+    check_alignment(ps, elem, streams, "one tensor");
     if (pl.span) {
-      for (uint32_t wps : {1u, 2u}) check_chunk_walk(pl, cg, wps, "launched piece");
+      for (uint32_t wps : {1u, 2u}) check_chunk_walk(pl, cg, wps, "launched tensor");
     }
-    CHECK(ps.count == 1 && pl.lo == next, "pieces out of order at %llu", (unsigned long long)pl.lo);
-    CHECK((uint64_t)ps.edge_end[0] < kMaxLaunchEdges, "launch of %u edge tiles", ps.edge_end[0]);
+    CHECK(ps.count == 1 && pl.lo == offset && (u128)pl.hi == (u128)offset + n, "another range");
     CHECK((u128)ps.edge_end[0] == (u128)pl.head_nt + pl.tail_nt, "edge count");
-    const uintptr_t at = addr + (uintptr_t)((pl.lo - offset) * elem);
-    CHECK(reinterpret_cast<uintptr_t>(pl.base) == at, "piece address");
-    check_plan(at, pl.lo, pl.hi - pl.lo, elem, cg);
-    next = (u128)pl.hi;
+    CHECK(reinterpret_cast<uintptr_t>(pl.base) == addr, "address");
+    check_plan(addr, offset, n, elem, cg);
     ++plans;
     return static_cast<int>(ZO_OK);
   });
-  CHECK(rc == ZO_OK && next == (u128)offset + n, "pieces cover up to %llu of %llu", (unsigned long long)(next - offset),
-        (unsigned long long)n);
-  if (groups_aligned(seg.params, offset, elem))
-    CHECK(plans == 1, "an aligned tensor in %zu launches", plans);
-  else
-    CHECK(plans == (n + kPieceElems - 1) / kPieceElems, "%zu pieces", plans);
+  CHECK(rc == ZO_OK && plans == 1, "a tensor in %zu launches", plans);
 }
 
 static void check_plans() {
@@ -229,8 +222,8 @@ static void check_plans() {
     for (uint32_t cg : {1u, 8u, 16u})
       for (uint64_t n : {ZO_N_MAX - 1, ZO_N_MAX - 1024, (1ull << 39) + 5, (1ull << 31) + 777})
         for (uint64_t off : {(uint64_t)0, (uint64_t)1023, (uint64_t)(1ull << 33) + 1, top - n, top - n - 5000}) {
-          check_pieces(A, off, n, elem, cg, 16);
-          check_pieces(A + elem, off, n, elem, cg);
+          check_one(A, off, n, elem, cg, 16);
+          check_one(A + elem, off, n, elem, cg);
         }
   // random cases
   for (int i = 0; i < 3000; ++i) {
@@ -240,8 +233,9 @@ static void check_plans() {
     uint64_t off = rnd() >> (rnd() % 64);
     if (off > top - n) off = top - n;
     // bases anywhere in a 128 KiB window, so that the alignment slots take every value
-    const uint32_t streams = 1u << (rnd() % 5);
-    check_pieces(A + (rnd() % 65536) * elem, off, n, elem, cg, streams);
+    const uint32_t all[] = {1, 2, 4, 8, 12, 16};
+    const uint32_t streams = all[rnd() % 6];
+    check_one(A + (rnd() % 65536) * elem, off, n, elem, cg, streams);
   }
 }
 
@@ -258,27 +252,35 @@ static void check_batches() {
     g += n + rnd() % 3;
   }
   CHECK(check_segments(segs.data(), (uint32_t)segs.size(), ZO_BF16) == ZO_OK, "disjoint segments rejected");
-  std::vector<size_t> seen;
-  size_t launches = 0;
-  int rc = plan_segments<kSegsPerLaunch>(segs.data(), (uint32_t)segs.size(), 2, 16, 4, [&](const Plans<kSegsPerLaunch>& ps) {
-    ++launches;
-    CHECK(ps.count >= 1 && ps.count <= kSegsPerLaunch, "batch of %u segments", ps.count);
-    check_alignment(ps, 2, 4, "batch");
-    for (uint32_t s = 0; s < ps.count; ++s) {
-      for (size_t i = 0; i < segs.size(); ++i)
-        if (segs[i].params == ps.p[s].base && segs[i].n) seen.push_back(i);
-      const uint32_t prev = s ? ps.chunk_end[s - 1] : 0;
-      CHECK(ps.chunk_end[s] - prev == plan_chunks(ps.p[s], 16), "chunk count of segment %u", s);
-      CHECK(ps.edge_end[s] - (s ? ps.edge_end[s - 1] : 0) == ps.p[s].head_nt + ps.p[s].tail_nt, "edge count");
-    }
-    return ZO_OK;
-  });
-  CHECK(rc == ZO_OK, "plan_segments status %d", rc);
-  size_t nonempty = 0;
+  size_t launches = 0, nonempty = 0;
   for (auto& s : segs) nonempty += s.n != 0;
-  CHECK(seen.size() == nonempty, "%zu of %zu segments launched", seen.size(), nonempty);
-  for (size_t i = 1; i < seen.size(); ++i) CHECK(seen[i] > seen[i - 1], "segments out of order");
-  CHECK(launches == (nonempty + kSegsPerLaunch - 1) / kSegsPerLaunch, "%zu launches", launches);
+  int rc = ZO_OK;
+  for (uint32_t streams : {1u, 2u, 4u, 8u, 12u, 16u})
+    for (bool any : {true, false}) {
+      std::vector<size_t> seen;
+      launches = 0;
+      rc = plan_segments<kSegsPerLaunch>(segs.data(), (uint32_t)segs.size(), 2, 16, streams, [&](const Plans<kSegsPerLaunch>& ps) {
+        ++launches;
+        CHECK(ps.count >= 1 && ps.count <= kSegsPerLaunch, "batch of %u segments", ps.count);
+        check_alignment(ps, 2, streams, "batch");
+        for (uint32_t s = 0; s < ps.count; ++s) {
+          const Plan& pl = ps.p[s];
+          for (size_t i = 0; i < segs.size(); ++i)
+            if (segs[i].params == pl.base && segs[i].n) seen.push_back(i);
+          const uint32_t prev = s ? ps.chunk_end[s - 1] : 0;
+          CHECK(ps.chunk_end[s] - prev == plan_chunks(pl, 16), "chunk count of segment %u", s);
+          CHECK(ps.edge_end[s] - (s ? ps.edge_end[s - 1] : 0) == pl.head_nt + pl.tail_nt, "edge count");
+          const bool fits = (pl.lo + kGroupElems - 1) / kGroupElems < pl.hi / kGroupElems;
+          CHECK((pl.span != 0) == (fits && (any || groups_aligned(pl.base, pl.lo, 2))), "row groups of segment %u", s);
+          check_chunk_walk(pl, 16, 1, "batch");
+        }
+        return ZO_OK;
+      }, any);
+      CHECK(rc == ZO_OK, "plan_segments status %d", rc);
+      CHECK(seen.size() == nonempty, "%zu of %zu segments launched", seen.size(), nonempty);
+      for (size_t i = 1; i < seen.size(); ++i) CHECK(seen[i] > seen[i - 1], "segments out of order");
+      CHECK(launches == (nonempty + kSegsPerLaunch - 1) / kSegsPerLaunch, "%zu launches", launches);
+    }
 
   // 40 tensors of ZO_N_MAX - 1 bf16 weights in 32 KiB chunks: 2^26 + 1 chunks each, so a launch
   // must close before 2^31 chunks
@@ -366,7 +368,7 @@ static void check_validation() {
 }
 
 static void check_grids_and_shapes() {
-  for (uint32_t block : {256u, 512u, 1024u})
+  for (uint32_t block : {128u, 256u, 512u, 768u, 1024u})
     for (uint64_t items : {(uint64_t)1, (uint64_t)1000, (uint64_t)1 << 26, (uint64_t)1 << 31, (uint64_t)1 << 40})
       for (uint64_t per : {(uint64_t)1, (uint64_t)4, (uint64_t)16, (uint64_t)block})
         for (bool sized : {false, true}) {

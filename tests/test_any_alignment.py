@@ -1,5 +1,6 @@
 """Tensors stored at any weight's address (a shard that starts at an odd global index, a view
-in the middle of a buffer): the full row groups take the vector path wherever they lie."""
+in the middle of a buffer): small launches sweep them element by element, in larger ones the full row
+groups take the vector path wherever they lie."""
 
 import os
 import shutil
@@ -63,3 +64,39 @@ def test_any_alignment_matches_oracle(dtype, shift, n, offset):
     whole = get(buf)
     np.testing.assert_array_equal(whole[:GUARD + shift], host[:GUARD + shift])
     np.testing.assert_array_equal(whole[GUARD + shift + n:], host[GUARD + shift + n:])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,shift", [("bf16", s) for s in range(1, 8)] + [("f32", s) for s in (1, 2, 3)])
+@pytest.mark.parametrize("n,offset,K", [(2 ** 20 + 2 ** 19 + 5, 1023, 9), (5_300_021, 2 ** 35 + 7, 133)])
+def test_row_groups_at_any_alignment(dtype, shift, n, offset, K):
+    """Launches large enough for row groups: the perturb and the update equal those of the same weights in aligned
+    storage bit for bit, the weights around the view stay, and the ends and middle match the oracle."""
+    f32 = dtype == "f32"
+    g = torch.Generator(device="cuda").manual_seed(shift)
+    buf = torch.empty(n + 2 * GUARD, device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
+    buf.normal_(0.0, 0.02, generator=g)
+    bits = torch.int32 if f32 else torch.int16
+    before = buf.clone()
+    view = buf[GUARD + shift:GUARD + shift + n]
+    room = torch.empty(n + 16, device="cuda", dtype=buf.dtype)
+    at = -(room.data_ptr() // room.element_size() - offset) % 8  # element `offset` where an aligned vector has it
+    aligned = room[at:at + n].copy_(view)
+    c = np.linspace(-0.4, 0.5, K).astype(np.float32)
+
+    def host(t):
+        return t.cpu().numpy() if f32 else t.view(torch.int16).cpu().numpy().view(np.uint16)
+
+    for t in (view, aligned):
+        zo.zo_perturb(t, 11, 1e-3, 77, 5, offset=offset)
+    same = torch.equal(view.view(bits), aligned.view(bits))
+    assert same
+    for a in (0, n // 2, n - 3000):
+        want = oracle.perturb(host(before[GUARD + shift + a:GUARD + shift + a + 3000]), dtype, offset + a, 77, 5, 11, 1e-3)
+        np.testing.assert_array_equal(host(view[a:a + 3000]), want)
+    for t in (view, aligned):
+        zo.zo_update_ex(t, c, 1e-3, 77, 5, offset=offset)
+    same = torch.equal(view.view(bits), aligned.view(bits))
+    assert same
+    for part in (slice(0, GUARD + shift), slice(GUARD + shift + n, None)):
+        assert torch.equal(buf[part].view(bits), before[part].view(bits))
