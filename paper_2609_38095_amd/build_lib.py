@@ -21,7 +21,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops off: no v_pk_{add,mul,fma}_f32 in the device code.
 DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-SWEEP_PARTS = 5  # zo_sweep.hip's ZO_PART: the entry points, and the kernels of four kinds of sweep
+SWEEP_PARTS = 9  # zo_sweep.hip's ZO_PART: the entry points, the kernels of four kinds of sweep, their folded updates
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math"]
 
 
@@ -50,7 +50,7 @@ def build(verbose=False):
         elif name.endswith(".cpp"):
             objs.append(os.path.join(BUILD, name + ".o"))
             cmds.append([cxx, *HOST_FLAGS, "-I", INCLUDE, "-c", src, "-o", objs[-1]])
-    with ThreadPoolExecutor(SWEEP_PARTS) as pool:
+    with ThreadPoolExecutor(8) as pool:
         list(pool.map(lambda cmd: _run(cmd, verbose), cmds))
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp, *objs], verbose)

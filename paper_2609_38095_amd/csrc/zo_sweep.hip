@@ -440,9 +440,9 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], float* tab, const
 // is folded into that group's table (see build_tables), so the per-element work is the plain
 // update's; kPerElement, r lies outside them and is applied per element as t =
 // fl(theta + delta_r), then t minus the sum of the table values, its generator words made
-// after the group loop. kMaybeFolded: kFolded when r's weight is not zero, else kNoRestore, for
-// the group counts that keep one kernel for both.
-enum RestoreMode { kNoRestore = 0, kFolded = 1, kPerElement = 2, kMaybeFolded = 3 };
+// after the group loop. Each is a kernel of its own: asked for at run time, the fold costs every table
+// build 40 to 60 ns a group (K = 133 on 100 weights: 18.1 -> 18.8 us, in fp32 17.8 -> 18.9).
+enum RestoreMode { kNoRestore = 0, kFolded = 1, kPerElement = 2 };
 
 template <class S, int NG, int RESTORE, int N, int C, int BLOCK, int WPS, int PACE = 0, int AHEAD = 0>
 __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uint32_t k_base, uint32_t K,
@@ -454,8 +454,7 @@ __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uin
   float* tab = NG > 0 ? tab_fix : tab_dyn;
   const uint32_t g_first = k_base / 8;
   // the table a folded restore changes (none: a group index no table has; below g_first wraps)
-  const bool folds = RESTORE == kFolded || (RESTORE == kMaybeFolded && r.eps != 0.0f);
-  const uint32_t fold_g = folds ? r.group - g_first : 0xFFFFFFFFu;
+  const uint32_t fold_g = RESTORE == kFolded ? r.group - g_first : 0xFFFFFFFFu;
   // the tables are built while each wave's first loads are in flight (for_each_group's prologue)
   auto build = [&]() { build_tables<NG, C, BLOCK>(tab, cf, k_base, K, n_groups, lr, fold_g, r); };
   // the lane's copy of a spread table (byte 0) and the second plane's offset (byte 2)
@@ -507,7 +506,6 @@ __global__ __launch_bounds__(kBlock) void gen_bits_kernel(uint8_t* out, uint64_t
 // Host side.
 [[maybe_unused]] int launch_status() { return hipGetLastError() == hipSuccess ? ZO_OK : ZO_ERR_HIP; }
 
-#if ZO_HAS_PART(1) || ZO_HAS_PART(2) || ZO_HAS_PART(3) || ZO_HAS_PART(4)
 // A workgroup's LDS above 64 KiB (static plus dynamic) must be allowed per kernel before the
 // launch.
 template <class K>
@@ -527,21 +525,147 @@ struct Dims {
 template <int V>
 using Int = std::integral_constant<int, V>;
 
+// The grid of a launch with B threads per workgroup and W waves per stream.
+template <int N>
+dim3 grid_of(const Plans<N>& ps, const Shape& sh, uint32_t B, uint32_t W) {
+  Shape s = sh;
+  s.block = B;
+  s.wps = W;
+  return dim3(plans_grid(ps, s));
+}
+
+// One update kernel: NG groups fixed at compile time (0: a runtime count, tables in dynamic LDS), C
+// copies of each table (of the first eight groups' tables from the ninth group on), B threads, W waves
+// per stream.
+template <class S, int NG, int MODE, int N, int C, int B, int W, int PACE, int AHEAD>
+void launch_kernel(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
+  auto kernel = update_kernel<S, NG, MODE, N, C, B, W, PACE, AHEAD>;
+  const size_t table_bytes = NG > 0 ? size_t{table_floats<NG, C>()} * sizeof(float)
+                                    : static_cast<size_t>(w.n_groups) * 256 * sizeof(float);
+  const size_t static_lds = NG > 0 ? table_bytes : 0;
+  const size_t pad = occupancy_lds(sh.blocks_per_cu, static_lds);
+  const size_t tables = NG > 0 ? 0 : table_bytes;
+  const size_t lds = tables > pad ? tables : pad;  // dynamic tables (up to 128 KiB) or the pad
+  allow_lds(kernel, lds, static_lds);
+  kernel<<<grid_of(ps, sh, B, W), dim3(B), lds, st>>>(ps, gen, w.k_base, w.K, w.n_groups, w.cf, w.lr, w.r);
+}
+
+}  // namespace
+
+namespace zo {
+
+// An update without a restore probe, or with one in its own groups: the kernel for its group count.
+template <class S, int N, int MODE>
+void launch_update(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
+  auto launch = [&](auto groups, auto copies_c, auto dims, auto pace, auto ahead) {
+    using D = decltype(dims);
+    launch_kernel<S, decltype(groups)::value, MODE, N, decltype(copies_c)::value, D::block, D::wps,
+                  decltype(pace)::value, decltype(ahead)::value>(ps, gen, w, sh, st);
+  };
+  using D256 = Dims<kBlock, 1>;
+  const Int<0> c0{}, unpaced{}, one_or_two_ahead{};
+  const bool spread = sh.copies || sh.mixed;
+  constexpr bool bf16 = sizeof(typename S::storage) == 2;
+  // three, five to seven and nine to sixteen groups (an odd count above eight runs with the next
+  // even one, its last table zero). A count fixed at compile time makes each table's offset an
+  // immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
+  // lets the compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU
+  // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
+  // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7.
+  auto other = [&](auto groups) {
+    constexpr int NG = decltype(groups)::value;
+    if (!spread) return launch(groups, c0, D256{}, unpaced, Int<1>{});
+    if constexpr (NG == 3) {
+      if constexpr (bf16) launch(groups, Int<16>{}, D256{}, unpaced, Int<2>{});
+    } else if constexpr (NG < 8) {
+      launch(groups, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
+    } else if constexpr (bf16) {
+      launch(groups, Int<16>{}, Dims<NG <= 12 ? 1024 : 768, 1>{}, unpaced, Int<1>{});
+    }
+  };
+  // The tables and launch dimensions shape_for picks for each group count. bf16 updates of one and
+  // two groups are paced at four outstanding memory operations, as the one-probe perturb.
+  switch (w.n_groups) {
+    case 1:
+      if constexpr (!bf16) {
+        if (spread) return launch(Int<1>{}, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
+      }
+      return launch(Int<1>{}, c0, D256{}, Int<bf16 ? 4 : 0>{}, one_or_two_ahead);
+    case 2:
+      if (!spread) return launch(Int<2>{}, c0, D256{}, unpaced, one_or_two_ahead);
+      if constexpr (bf16)
+        return launch(Int<2>{}, Int<32>{}, Dims<512, 2>{}, Int<4>{}, one_or_two_ahead);
+      else
+        return launch(Int<2>{}, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
+    case 3:
+      return other(Int<3>{});
+    case 4:
+      if (!spread) return launch(Int<4>{}, c0, D256{}, unpaced, one_or_two_ahead);
+      if constexpr (bf16)
+        return launch(Int<4>{}, Int<16>{}, Dims<512, 1>{}, unpaced, Int<2>{});
+      else
+        return launch(Int<4>{}, Int<16>{}, D256{}, unpaced, Int<1>{});
+    case 5:
+      return other(Int<5>{});
+    case 6:
+      return other(Int<6>{});
+    case 7:
+      return other(Int<7>{});
+    case 8:
+      if (!spread) return launch(Int<8>{}, c0, D256{}, unpaced, one_or_two_ahead);
+      return launch(Int<8>{}, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
+    case 9:
+    case 10:
+      return other(Int<10>{});
+    case 11:
+    case 12:
+      return other(Int<12>{});
+    case 13:
+    case 14:
+      return other(Int<14>{});
+    case 15:
+    case 16:
+      return other(Int<16>{});
+    default:
+      return launch(Int<0>{}, c0, D256{}, unpaced, one_or_two_ahead);
+  }
+}
+
+// The library compiles this file once per part (ZO_PART 0 to 8; all at once when it is not defined),
+// so that the kernels build in parallel: part 0 holds the entry points, 1 to 4 the sweeps of one storage
+// type over one tensor or a list, 5 to 8 their updates with a folded restore.
+#if defined(ZO_PART)
+#define ZO_FOLDED(S, N) \
+  template void launch_update<S, N, kFolded>(const Plans<N>&, const Gen&, const Sweep&, const Shape&, hipStream_t);
+#if ZO_HAS_PART(5)
+ZO_FOLDED(F32, 1)
+#elif ZO_HAS_PART(6)
+ZO_FOLDED(BF16, 1)
+#elif ZO_HAS_PART(7)
+ZO_FOLDED(F32, kSegsPerLaunch)
+#elif ZO_HAS_PART(8)
+ZO_FOLDED(BF16, kSegsPerLaunch)
+#else
+extern ZO_FOLDED(F32, 1)
+extern ZO_FOLDED(BF16, 1)
+extern ZO_FOLDED(F32, kSegsPerLaunch)
+extern ZO_FOLDED(BF16, kSegsPerLaunch)
+#endif
+#endif
+
+}  // namespace zo
+
+namespace {
+
+#if ZO_HAS_PART(1) || ZO_HAS_PART(2) || ZO_HAS_PART(3) || ZO_HAS_PART(4)
+
 template <class S, int N>
 void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
-  const uint32_t cap = sh.blocks_per_cu;
-  // the grid of a launch with B threads per workgroup and W waves per stream
-  auto grid_of = [&](uint32_t B, uint32_t W) {
-    Shape s = sh;
-    s.block = B;
-    s.wps = W;
-    return dim3(plans_grid(ps, s));
-  };
   if (!w.update) {
-    const size_t pad = occupancy_lds(cap, 0);
+    const size_t pad = occupancy_lds(sh.blocks_per_cu, 0);
     auto go = [&](auto kernel, Probe b, uint32_t block = kBlock) {
       allow_lds(kernel, pad);
-      kernel<<<grid_of(block, 1), dim3(block), pad, st>>>(ps, gen, w.a, b);
+      kernel<<<grid_of(ps, sh, block, 1), dim3(block), pad, st>>>(ps, gen, w.a, b);
     };
     // paced when the generator work per byte is lightest: one probe group, or fp32 with two;
     // at 4 outstanding operations (bf16: one probe +1.3%, two in one group +3.4% over 2; fp32
@@ -561,112 +685,13 @@ void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shap
       paced ? go(perturb_kernel<S, false, N, 4, kBlock, 1>, w.a) : go(perturb_kernel<S, false, N, 0, kBlock, 1>, w.a);
     return;
   }
-  // One kernel: NG groups fixed at compile time (0: a runtime count, tables in dynamic LDS), C
-  // copies of each table, launched with the dimensions it was built for.
-  auto go = [&](auto kernel, auto groups, auto copies_c, auto dims) {
-    constexpr int NG = decltype(groups)::value, C = decltype(copies_c)::value;
-    constexpr int B = decltype(dims)::block, W = decltype(dims)::wps;
-    const size_t table_bytes = NG > 0 ? size_t{table_floats<NG, C>()} * sizeof(float)
-                                      : static_cast<size_t>(w.n_groups) * 256 * sizeof(float);
-    const size_t static_lds = NG > 0 ? table_bytes : 0;
-    const size_t pad = occupancy_lds(cap, static_lds);
-    const size_t tables = NG > 0 ? 0 : table_bytes;
-    const size_t lds = tables > pad ? tables : pad;  // dynamic tables (up to 128 KiB) or the pad
-    allow_lds(kernel, lds, static_lds);
-    kernel<<<grid_of(B, W), dim3(B), lds, st>>>(ps, gen, w.k_base, w.K, w.n_groups, w.cf, w.lr, w.r);
-  };
-  // Calls go for the kernel of NG groups, restore mode M, C copies of each table (of the first
-  // eight groups' tables from the ninth group on), B threads, W waves per stream.
-  auto launch = [&](auto groups, auto mode, auto copies_c, auto dims, auto pace, auto ahead) {
-    using D = decltype(dims);
-    go(update_kernel<S, decltype(groups)::value, static_cast<int>(decltype(mode)::value), N, decltype(copies_c)::value,
-                     D::block, D::wps, decltype(pace)::value, decltype(ahead)::value>,
-       groups, copies_c, dims);
-  };
-  using D256 = Dims<kBlock, 1>;
-  const Int<0> c0{}, unpaced{}, one_or_two_ahead{};
-  const bool spread = sh.copies || sh.mixed;
   // a restore probe outside the update's groups: the per-element restore, runtime group count
-  if (w.restore && !w.fold) {
-    launch(Int<0>{}, Int<kPerElement>{}, c0, D256{}, unpaced, one_or_two_ahead);
-    return;
-  }
-  constexpr bool bf16 = sizeof(typename S::storage) == 2;
-  // The tables and launch dimensions shape_for picks for each group count. bf16 updates of one and
-  // two groups are paced at four outstanding memory operations, as the one-probe perturb. With one,
-  // two, four and eight groups a folded restore runs the same code in an instantiation of its
-  // own, so that profiles tell the two calls apart.
-  auto dispatch = [&](auto mode) {
-    switch (w.n_groups) {
-      case 1:
-        if constexpr (!bf16) {
-          if (spread) return launch(Int<1>{}, mode, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
-        }
-        return launch(Int<1>{}, mode, c0, D256{}, Int<bf16 ? 4 : 0>{}, one_or_two_ahead);
-      case 2:
-        if (!spread) return launch(Int<2>{}, mode, c0, D256{}, unpaced, one_or_two_ahead);
-        if constexpr (bf16)
-          return launch(Int<2>{}, mode, Int<32>{}, Dims<512, 2>{}, Int<4>{}, one_or_two_ahead);
-        else
-          return launch(Int<2>{}, mode, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
-      case 4:
-        if (!spread) return launch(Int<4>{}, mode, c0, D256{}, unpaced, one_or_two_ahead);
-        if constexpr (bf16)
-          return launch(Int<4>{}, mode, Int<16>{}, Dims<512, 1>{}, unpaced, Int<2>{});
-        else
-          return launch(Int<4>{}, mode, Int<16>{}, D256{}, unpaced, Int<1>{});
-      default:
-        if (!spread) return launch(Int<8>{}, mode, c0, D256{}, unpaced, one_or_two_ahead);
-        return launch(Int<8>{}, mode, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
-    }
-  };
-  // three, five to seven and nine to sixteen groups (an odd count above eight runs with the next
-  // even one, its last table zero). A count fixed at compile time makes each table's offset an
-  // immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
-  // lets the compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU
-  // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
-  // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7.
-  auto other = [&](auto groups) {
-    constexpr int NG = decltype(groups)::value;
-    const Int<kMaybeFolded> mode{};
-    if (!spread) return launch(groups, mode, c0, D256{}, unpaced, Int<1>{});
-    if constexpr (NG == 3) {
-      if constexpr (bf16) launch(groups, mode, Int<16>{}, D256{}, unpaced, Int<2>{});
-    } else if constexpr (NG < 8) {
-      launch(groups, mode, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
-    } else if constexpr (bf16) {
-      launch(groups, mode, Int<16>{}, Dims<NG <= 12 ? 1024 : 768, 1>{}, unpaced, Int<1>{});
-    }
-  };
-  switch (w.n_groups) {
-    case 1:
-    case 2:
-    case 4:
-    case 8:
-      return w.fold ? dispatch(Int<kFolded>{}) : dispatch(Int<kNoRestore>{});
-    case 3:
-      return other(Int<3>{});
-    case 5:
-      return other(Int<5>{});
-    case 6:
-      return other(Int<6>{});
-    case 7:
-      return other(Int<7>{});
-    case 9:
-    case 10:
-      return other(Int<10>{});
-    case 11:
-    case 12:
-      return other(Int<12>{});
-    case 13:
-    case 14:
-      return other(Int<14>{});
-    case 15:
-    case 16:
-      return other(Int<16>{});
-    default:
-      return launch(Int<0>{}, Int<kMaybeFolded>{}, c0, D256{}, unpaced, one_or_two_ahead);
-  }
+  if (w.restore && !w.fold)
+    launch_kernel<S, 0, kPerElement, N, 0, kBlock, 1, 0, 0>(ps, gen, w, sh, st);
+  else if (w.fold)
+    launch_update<S, N, kFolded>(ps, gen, w, sh, st);
+  else
+    launch_update<S, N, kNoRestore>(ps, gen, w, sh, st);
 }
 
 // One contiguous tensor.
@@ -703,9 +728,7 @@ int run_segments(const zo_segment* segs, uint32_t n_segs, uint64_t seed, uint32_
 
 }  // namespace
 
-// The sweeps of one storage type over one tensor or a list, each a part of its own: the library
-// compiles this file once per part (ZO_PART 0 to 4; all at once when it is not defined), so that
-// the kernels of the four build in parallel.
+// The sweeps of one storage type over one tensor or a list, each a part of its own.
 namespace zo {
 int sweep_flat_f32(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* st);
 int sweep_flat_bf16(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* st);
