@@ -566,12 +566,13 @@ void launch_update(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Sha
   const Int<0> c0{}, unpaced{}, one_or_two_ahead{};
   const bool spread = sh.copies || sh.mixed;
   constexpr bool bf16 = sizeof(typename S::storage) == 2;
-  // three, five to seven and nine to sixteen groups (an odd count above eight runs with the next
-  // even one, its last table zero). A count fixed at compile time makes each table's offset an
-  // immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
+  // three, five to seven and nine to sixteen groups. A count fixed at compile time makes each table's
+  // offset an immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
   // lets the compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU
   // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
-  // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7.
+  // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7. Odd counts have kernels of their
+  // own too: run with a zero table as the next even one, K = 72 took 70.7 us there against 62.0, and on 100
+  // weights, where the run-time loop takes 11.4 us, 12.1 against 11.3.
   auto other = [&](auto groups) {
     constexpr int NG = decltype(groups)::value;
     if (!spread) return launch(groups, c0, D256{}, unpaced, Int<1>{});
@@ -615,15 +616,19 @@ void launch_update(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Sha
       if (!spread) return launch(Int<8>{}, c0, D256{}, unpaced, one_or_two_ahead);
       return launch(Int<8>{}, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
     case 9:
+      return other(Int<9>{});
     case 10:
       return other(Int<10>{});
     case 11:
+      return other(Int<11>{});
     case 12:
       return other(Int<12>{});
     case 13:
+      return other(Int<13>{});
     case 14:
       return other(Int<14>{});
     case 15:
+      return other(Int<15>{});
     case 16:
       return other(Int<16>{});
     default:
