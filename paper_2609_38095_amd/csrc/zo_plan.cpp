@@ -208,56 +208,20 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   }
   if (w.restore && !w.fold) return short_chunks(elem);
   const uint32_t g = w.n_groups;
-  Shape sh{chunk, 1, 0};
-  auto four_chunks = [&](uint32_t block) {
-    auto rounds = [&](uint64_t chunks) {  // memory may cut one workgroup's block off the first
-      return ceil_div(elements * elem / (chunks * kMaxChunkBytes * (block / 64)) + 1, kCUs);
-    };
-    return 400 * rounds(4) <= (elem == 2 ? 102 : 110) * rounds(1);
-  };
-  if (elem == 4) {
-    if (g <= 2) {  // 32-copy tables
-      sh.copies = 32;
-    } else if (g == 4) {
-      sh.copies = 16;
-      sh.blocks_per_cu = 2;
-    } else if (g >= 5 && g <= 8) {
-      sh.copies = 16;
-      sh.block = 512;
-      sh.chunks_per_wave = g == 8 && four_chunks(sh.block) ? 4 : 1;
-    } else if (g > 8) {
-      return short_chunks(elem);
-    }
+  const SpreadDims d = spread_dims(elem, g);
+  if (g > 4 && d.copies == 0) return short_chunks(elem);
+  Shape sh{chunk, 1, 0, d.block, d.wps, d.copies};
+  if (g == 4 || (g == 3 && elem == 2)) sh.blocks_per_cu = 2;
+  if (g <= 4) {
+    if (elem == 2 && g != 3) sh.chunks_per_wave = 1;
     return sh;
   }
-  switch (g) {
-    case 1:
-      sh.chunks_per_wave = 1;  // one shared table: a single group leaves the LDS half idle
-      return sh;
-    case 2:
-      sh.copies = 32;
-      sh.wps = 2;
-      sh.chunks_per_wave = 1;
-      sh.block = 512;
-      return sh;
-    case 3:
-      sh.copies = 16;
-      sh.blocks_per_cu = 2;
-      return sh;
-    case 4:
-      sh.copies = 16;
-      sh.block = 512;
-      sh.blocks_per_cu = 2;
-      sh.chunks_per_wave = 1;
-      return sh;
-    default:
-      if (g > 16) return short_chunks(elem);
-      sh.copies = g <= 8 ? 16 : 0;
-      sh.mixed = g > 8;
-      sh.block = g > 12 ? 768 : 1024;
-      sh.chunks_per_wave = four_chunks(sh.block) ? 4 : 1;
-      return sh;
-  }
+  auto rounds = [&](uint64_t chunks) {  // memory may cut one workgroup's block off the first
+    return ceil_div(elements * elem / (chunks * kMaxChunkBytes * (sh.block / 64)) + 1, kCUs);
+  };
+  const bool four = (elem == 2 || g == 8) && 400 * rounds(4) <= (elem == 2 ? 102 : 110) * rounds(1);
+  sh.chunks_per_wave = four ? 4 : 1;
+  return sh;
 }
 
 // Shape of one launch of a list call. The call's weights decide whether it streams; its launches take
@@ -273,9 +237,8 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
 // of each other either way; of 533 MiB (2.6 GB, bf16, K = 96) the streaming one takes 2,659 us, the
 // other 2,751.
 Shape list_shape(uint64_t call_elements, uint64_t launch_elements, size_t elem, const Sweep& w) {
-  const bool fixed_count = w.update && !(w.restore && !w.fold) && w.n_groups <= (elem == 2 ? 16u : 8u);
-  if (fixed_count && w.n_groups >= 5 && call_elements * elem >= kStreamBytes &&
-      launch_elements * elem < kStreamBytes)
+  const bool large_blocks = w.update && !(w.restore && !w.fold) && w.n_groups >= 5 && spread_dims(elem, w.n_groups).copies;
+  if (large_blocks && call_elements * elem >= kStreamBytes && launch_elements * elem < kStreamBytes)
     return launch_elements * elem < kShortLaunchBytes ? short_chunks(elem) : shape_for(launch_elements, elem, w);
   Shape sh = shape_for(call_elements, elem, w);
   if (sh.chunks_per_wave > 1) sh.chunks_per_wave = 1;

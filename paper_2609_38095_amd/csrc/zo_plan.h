@@ -98,9 +98,44 @@ struct Shape {
   uint32_t chunks_per_wave;  // 0: up to kDefaultMaxBlocks workgroups, grid-stride beyond
   uint32_t block = kBlock;   // threads per workgroup
   uint32_t wps = 1;          // waves per stream (per chunk)
-  uint32_t copies = 0;       // update: copies of each table (0: one shared table)
-  bool mixed = false;        // update of more than eight groups: 16 copies of the first eight tables
+  uint32_t copies = 0;       // update: copies of each spread table (0: shared tables)
 };
+
+// The kernel of a streaming update on spread tables, by weight type and probe groups: copies of each table
+// (0: there is none, the count runs on shared tables), threads per workgroup and waves per stream. The
+// planner and the kernels' dispatch both take it from here.
+struct SpreadDims {
+  uint32_t copies, block, wps;
+};
+constexpr SpreadDims spread_dims(size_t elem, uint32_t groups) {
+  if (elem == 4) {
+    if (groups <= 2) return {32, 256, 1};
+    if (groups == 4) return {16, 256, 1};
+    if (groups >= 5 && groups <= 8) return {16, 512, 1};
+  } else {
+    if (groups == 2) return {32, 512, 2};
+    if (groups == 3) return {16, 256, 1};
+    if (groups == 4) return {16, 512, 1};
+    if (groups >= 5 && groups <= 16) return {16, groups <= 12 ? 1024u : 768u, 1};
+  }
+  return {0, kBlock, 1};
+}
+
+// Spread tables of a kernel for a fixed group count: interleaved copies, in planes of 64 KiB, at most
+// two (zo_sweep.hip). The first 8 groups are spread; from the ninth on a group has one shared table,
+// behind the spread ones.
+constexpr uint32_t kSpreadFloats = 256 * 64;  // one plane
+constexpr uint32_t kSpreadGroups = 8;
+constexpr uint32_t spread_groups(uint32_t groups, uint32_t copies) {
+  return copies == 0 ? 0 : groups < kSpreadGroups ? groups : kSpreadGroups;
+}
+constexpr uint32_t shared_base(uint32_t groups, uint32_t copies) {  // floats of the spread tables
+  return copies == 0 ? 0 : (spread_groups(groups, copies) * copies <= 64 ? 1 : 2) * kSpreadFloats;
+}
+// floats of all tables of `groups` groups
+constexpr uint32_t table_floats(uint32_t groups, uint32_t copies) {
+  return shared_base(groups, copies) + (groups - spread_groups(groups, copies)) * 256;
+}
 
 // Whether global element 0 of a tensor stored from params with global offset `offset` would
 // sit at a 16-byte boundary, i.e. whether the vectors of its row groups are 16-byte aligned.

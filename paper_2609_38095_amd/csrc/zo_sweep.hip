@@ -213,32 +213,13 @@ __global__ __launch_bounds__(BLOCK) void perturb_kernel(Plans<N> ps, Gen gen, Pr
 // byte permute of the generator word and the lane's offset word (byte 0: 4 (l mod C), byte 2:
 // 1, selected for the second plane), plus an immediate offset: as many instructions as a
 // lookup into a shared table.
-constexpr uint32_t kSpreadFloats = 256 * 64;  // one plane
 template <int C>
 constexpr uint32_t groups_per_plane() {
   return C > 0 ? 64 / C : 1;
 }
-// A kernel of NG groups spreads the first 8 of them; from the ninth on a group has one shared
-// table, behind the spread ones (K = 72 to 128, see group_sums).
-constexpr int kSpreadGroups = 8;
-template <int NG, int C>
-constexpr uint32_t spread_groups() {
-  return C == 0 ? 0 : NG < kSpreadGroups ? NG : kSpreadGroups;
-}
-template <int NG, int C>
-constexpr uint32_t shared_base() {  // floats of the spread tables
-  return C == 0 ? 0 : (spread_groups<NG, C>() * C <= 64 ? 1 : 2) * kSpreadFloats;
-}
-// floats of the tables of NG groups: C interleaved copies, or one shared copy (C = 0)
-template <int NG, int C>
-constexpr uint32_t table_floats() {
-  static_assert(C == 0 || ((C == 16 || C == 32) && spread_groups<NG, C>() * C <= 128),
-                "spread tables fill at most two planes");
-  return shared_base<NG, C>() + (NG - spread_groups<NG, C>()) * 256;
-}
 template <int NG, int C>
 __device__ __forceinline__ float* shared_table(float* tab, uint32_t g) {
-  return tab + shared_base<NG, C>() + 256u * (g - spread_groups<NG, C>());
+  return tab + shared_base(NG, C) + 256u * (g - spread_groups(NG, C));
 }
 
 // Build the n_groups x 256 table in LDS (C > 0: the interleaved copies). Entry (g, b):
@@ -274,7 +255,7 @@ __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32
     }
     float t = (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) * lr;
     if (g == fold_g) t = t - delta(fold, b);
-    if (g < spread_groups<NG, C>()) {
+    if (g < spread_groups(NG, C)) {
       // entry b's C / 4 float4 of copies, 256 bytes after entry b - 1's: thread b writes them
       // starting at float4 b mod (C / 4), so that the lanes of each write spread over the banks
       // the group's copies occupy (in a fixed order all 64 would land on the same 4 banks)
@@ -413,7 +394,7 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], float* tab, const
       for (int j = 0; j < (int)kTile; ++j) {
         const uint32_t byte = word_byte(x[j >> 2], j & 3);
         float v;
-        if (g < spread_groups<NG, C>()) {
+        if (g < spread_groups(NG, C)) {
           constexpr uint32_t P = groups_per_plane<C>();
           v = tab[kSpreadFloats * (g / P) + 64u * byte + C * (g % P) + (threadIdx.x % (C > 0 ? C : 1))];
         } else {
@@ -447,13 +428,14 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], float* tab, const
 // build 40 to 60 ns a group (K = 133 on 100 weights: 18.1 -> 18.8 us, in fp32 17.8 -> 18.9).
 enum RestoreMode { kNoRestore = 0, kFolded = 1, kPerElement = 2 };
 
-template <class S, int NG, int RESTORE, int N, int C, int BLOCK, int WPS, int PACE = 0, int AHEAD = 0>
+template <class S, int NG, int RESTORE, int N, int C, int BLOCK, int WPS, int PACE, int AHEAD>
 __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uint32_t k_base, uint32_t K,
                                                       uint32_t n_groups, Coefs cf, float lr, Probe r) {
+  static_assert(C == 0 || ((C == 16 || C == 32) && spread_groups(NG, C) * C <= 128), "spread tables fill at most two planes");
   // n_groups x 256 floats (C > 0: the interleaved copies): static for a fixed group count
   // (constant LDS offsets), else dynamic.
   extern __shared__ float tab_dyn[];
-  __shared__ float tab_fix[NG > 0 ? table_floats<NG, C>() : 1];
+  __shared__ float tab_fix[NG > 0 ? table_floats(NG, C) : 1];
   float* tab = NG > 0 ? tab_fix : tab_dyn;
   const uint32_t g_first = k_base / 8;
   // the table a folded restore changes (none: a group index no table has; below g_first wraps)
@@ -463,10 +445,7 @@ __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uin
   // the lane's copy of a spread table (byte 0) and the second plane's offset (byte 2)
   const uint32_t lane_off = 4u * (threadIdx.x % (C > 0 ? C : 32)) | (1u << 16);
   constexpr int R = GroupShape<S>::kRows;
-  // two groups in flight with spread tables and for one, two or four groups; one for the
-  // other counts, which run at three or more workgroups per CU (AHEAD > 0 sets it)
-  constexpr int kAhead = AHEAD ? AHEAD : C > 0 || NG == 1 || NG == 2 || NG == 4 ? 2 : 1;
-  for_each_group<S, kAhead, N, PACE, BLOCK, WPS>(ps, [&](uint64_t vbase, u32x4 (&d)[R], uint32_t lane) {
+  for_each_group<S, AHEAD, N, PACE, BLOCK, WPS>(ps, [&](uint64_t vbase, u32x4 (&d)[R], uint32_t lane) {
     float acc[R][S::kVecElems];
     uint32_t Wr[R][S::kWords];  // the restore probe's words
     group_sums<S, NG, C>(acc, tab, gen, vbase, lane, n_groups, g_first, lane_off);
@@ -518,13 +497,6 @@ void allow_lds(K kernel, size_t dynamic_bytes, size_t static_bytes = 0) {
                               static_cast<int>(dynamic_bytes));
 }
 
-// Launch dimensions a kernel is built for: workgroup size and waves per stream. A kernel is
-// always launched with the dimensions it was built for.
-template <int B, int W>
-struct Dims {
-  static constexpr int block = B, wps = W;
-};
-
 template <int V>
 using Int = std::integral_constant<int, V>;
 
@@ -543,7 +515,7 @@ dim3 grid_of(const Plans<N>& ps, const Shape& sh, uint32_t B, uint32_t W) {
 template <class S, int NG, int MODE, int N, int C, int B, int W, int PACE, int AHEAD>
 void launch_kernel(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
   auto kernel = update_kernel<S, NG, MODE, N, C, B, W, PACE, AHEAD>;
-  const size_t table_bytes = NG > 0 ? size_t{table_floats<NG, C>()} * sizeof(float)
+  const size_t table_bytes = NG > 0 ? size_t{table_floats(NG, C)} * sizeof(float)
                                     : static_cast<size_t>(w.n_groups) * 256 * sizeof(float);
   const size_t static_lds = NG > 0 ? table_bytes : 0;
   const size_t pad = occupancy_lds(sh.blocks_per_cu, static_lds);
@@ -560,82 +532,64 @@ namespace zo {
 // An update without a restore probe, or with one in its own groups: the kernel for its group count.
 template <class S, int N, int MODE>
 void launch_update(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
-  auto launch = [&](auto groups, auto copies_c, auto dims, auto pace, auto ahead) {
-    using D = decltype(dims);
-    launch_kernel<S, decltype(groups)::value, MODE, N, decltype(copies_c)::value, D::block, D::wps,
-                  decltype(pace)::value, decltype(ahead)::value>(ps, gen, w, sh, st);
-  };
-  using D256 = Dims<kBlock, 1>;
-  const Int<0> c0{}, unpaced{}, one_or_two_ahead{};
-  const bool spread = sh.copies || sh.mixed;
   constexpr bool bf16 = sizeof(typename S::storage) == 2;
-  // three, five to seven and nine to sixteen groups. A count fixed at compile time makes each table's
+  // A count fixed at compile time: on the spread tables spread_dims gives it where the shape asks for them,
+  // else on shared ones. Streaming bf16 updates of one and two groups are paced at four outstanding memory
+  // operations, as the one-probe perturb. Two row groups are in flight with one, two and four groups and with
+  // spread tables, one otherwise and where two would spill registers (bf16 above eight groups, fp32 above two).
+  // The fixed count makes each table's
   // offset an immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
   // lets the compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU
   // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
   // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7. Odd counts have kernels of their
   // own too: run with a zero table as the next even one, K = 72 took 70.7 us there against 62.0, and on 100
   // weights, where the run-time loop takes 11.4 us, 12.1 against 11.3.
-  auto other = [&](auto groups) {
+  auto fixed = [&](auto groups) {
     constexpr int NG = decltype(groups)::value;
-    if (!spread) return launch(groups, c0, D256{}, unpaced, Int<1>{});
-    if constexpr (NG == 3) {
-      if constexpr (bf16) launch(groups, Int<16>{}, D256{}, unpaced, Int<2>{});
-    } else if constexpr (NG < 8) {
-      launch(groups, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
-    } else if constexpr (bf16) {
-      launch(groups, Int<16>{}, Dims<NG <= 12 ? 1024 : 768, 1>{}, unpaced, Int<1>{});
+    constexpr SpreadDims d = spread_dims(sizeof(typename S::storage), NG);
+    if constexpr (d.copies > 0) {
+      constexpr int kAhead = NG <= 2 || (bf16 && NG <= 8) ? 2 : 1;
+      if (sh.copies)
+        return launch_kernel<S, NG, MODE, N, d.copies, d.block, d.wps, bf16 && NG == 2 ? 4 : 0, kAhead>(ps, gen, w, sh, st);
     }
+    constexpr int kAhead = NG == 1 || NG == 2 || NG == 4 ? 2 : 1;
+    launch_kernel<S, NG, MODE, N, 0, kBlock, 1, bf16 && NG == 1 ? 4 : 0, kAhead>(ps, gen, w, sh, st);
   };
-  // The tables and launch dimensions shape_for picks for each group count. bf16 updates of one and
-  // two groups are paced at four outstanding memory operations, as the one-probe perturb.
   switch (w.n_groups) {
     case 1:
-      if constexpr (!bf16) {
-        if (spread) return launch(Int<1>{}, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
-      }
-      return launch(Int<1>{}, c0, D256{}, Int<bf16 ? 4 : 0>{}, one_or_two_ahead);
+      return fixed(Int<1>{});
     case 2:
-      if (!spread) return launch(Int<2>{}, c0, D256{}, unpaced, one_or_two_ahead);
-      if constexpr (bf16)
-        return launch(Int<2>{}, Int<32>{}, Dims<512, 2>{}, Int<4>{}, one_or_two_ahead);
-      else
-        return launch(Int<2>{}, Int<32>{}, D256{}, unpaced, one_or_two_ahead);
+      return fixed(Int<2>{});
     case 3:
-      return other(Int<3>{});
+      return fixed(Int<3>{});
     case 4:
-      if (!spread) return launch(Int<4>{}, c0, D256{}, unpaced, one_or_two_ahead);
-      if constexpr (bf16)
-        return launch(Int<4>{}, Int<16>{}, Dims<512, 1>{}, unpaced, Int<2>{});
-      else
-        return launch(Int<4>{}, Int<16>{}, D256{}, unpaced, Int<1>{});
+      return fixed(Int<4>{});
     case 5:
-      return other(Int<5>{});
+      return fixed(Int<5>{});
     case 6:
-      return other(Int<6>{});
+      return fixed(Int<6>{});
     case 7:
-      return other(Int<7>{});
+      return fixed(Int<7>{});
     case 8:
-      if (!spread) return launch(Int<8>{}, c0, D256{}, unpaced, one_or_two_ahead);
-      return launch(Int<8>{}, Int<16>{}, Dims<bf16 ? 1024 : 512, 1>{}, unpaced, Int<bf16 ? 2 : 1>{});
+      return fixed(Int<8>{});
     case 9:
-      return other(Int<9>{});
+      return fixed(Int<9>{});
     case 10:
-      return other(Int<10>{});
+      return fixed(Int<10>{});
     case 11:
-      return other(Int<11>{});
+      return fixed(Int<11>{});
     case 12:
-      return other(Int<12>{});
+      return fixed(Int<12>{});
     case 13:
-      return other(Int<13>{});
+      return fixed(Int<13>{});
     case 14:
-      return other(Int<14>{});
+      return fixed(Int<14>{});
     case 15:
-      return other(Int<15>{});
+      return fixed(Int<15>{});
     case 16:
-      return other(Int<16>{});
+      return fixed(Int<16>{});
     default:
-      return launch(Int<0>{}, c0, D256{}, unpaced, one_or_two_ahead);
+      return launch_kernel<S, 0, MODE, N, 0, kBlock, 1, 0, 1>(ps, gen, w, sh, st);
   }
 }
 
@@ -695,7 +649,7 @@ void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shap
   }
   // a restore probe outside the update's groups: the per-element restore, runtime group count
   if (w.restore && !w.fold)
-    launch_kernel<S, 0, kPerElement, N, 0, kBlock, 1, 0, 0>(ps, gen, w, sh, st);
+    launch_kernel<S, 0, kPerElement, N, 0, kBlock, 1, 0, 1>(ps, gen, w, sh, st);
   else if (w.fold)
     launch_update<S, N, kFolded>(ps, gen, w, sh, st);
   else

@@ -57,7 +57,7 @@ static void check_lists() {
             CHECK(ps.chunk_groups == sh.chunk_groups, "chunks of another shape");
             CHECK(sh.chunks_per_wave <= 1, "%u chunks per stream", sh.chunks_per_wave);
             if (groups >= 5 && bytes < kStreamBytes)
-              CHECK(sh.block == kBlock && sh.copies == 0 && !sh.mixed,
+              CHECK(sh.block == kBlock && sh.copies == 0,
                     "elem %zu, %u groups, a launch of %llu MiB in workgroups of %u threads", elem, groups,
                     (unsigned long long)(bytes >> 20), sh.block);
             if (groups >= 5 && bytes < kShortLaunchBytes) CHECK(sh.chunk_groups * kGroupElems * elem == 4096, "chunks");
@@ -127,7 +127,31 @@ static void check_misaligned() {
   }
 }
 
+// A shape that asks for spread tables is the one the kernel of its group count is built for (its workgroups,
+// on which the chunk alignment rests), any other has the default workgroups; and tables fit the LDS.
+static void check_kernels() {
+  for (size_t elem : {(size_t)2, (size_t)4})
+    for (uint32_t groups = 1; groups <= ZO_K_MAX / 8; ++groups) {
+      const Sweep w = update_of(groups);
+      const SpreadDims d = spread_dims(elem, groups);
+      for (uint64_t mib : {1, 200, 300, 800, 5000, 30000}) {
+        const uint64_t n = (static_cast<uint64_t>(mib) << 20) / elem;
+        for (const Shape& sh : {shape_for(n, elem, w), list_shape(n, n, elem, w), list_shape(n, n / 8, elem, w)}) {
+          if (sh.copies)
+            CHECK(sh.copies == d.copies && sh.block == d.block && sh.wps == d.wps, "elem %zu, %u groups", elem, groups);
+          else
+            CHECK(sh.block == kBlock && sh.wps == 1, "elem %zu, %u groups: %u threads on shared tables", elem, groups, sh.block);
+          CHECK(mib >= 256 || sh.copies == 0, "spread tables for a cache-sized buffer");
+          const size_t tables = 4 * static_cast<size_t>(table_floats(groups, sh.copies));
+          CHECK(tables + occupancy_lds(sh.blocks_per_cu, tables) <= 160 * 1024, "%zu bytes of tables", tables);
+          if (sh.copies) CHECK(spread_groups(groups, sh.copies) * sh.copies <= 128, "more than two planes");
+        }
+      }
+    }
+}
+
 int main() {
+  check_kernels();
   check_lists();
   check_misaligned();
   check_rounds();

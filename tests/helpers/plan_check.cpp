@@ -398,7 +398,7 @@ static void check_grids_and_shapes() {
           CHECK(sh.chunk_groups >= 1 && sh.chunk_groups * kGroupElems * elem <= kMaxChunkBytes, "chunk");
           CHECK(sh.block % 64 == 0 && sh.block <= 1024 && sh.wps >= 1 && (sh.block / 64) % sh.wps == 0, "dims");
           CHECK(sh.copies == 0 || sh.copies == 16 || sh.copies == 32, "copies");
-          CHECK(!w.update || sh.copies * w.n_groups <= 128, "tables beyond two planes");
+          CHECK(!w.update || 4 * table_floats(w.n_groups, sh.copies) <= 160 * 1024, "tables beyond the LDS");
           CHECK(occupancy_lds(sh.blocks_per_cu, 0) <= 96 * 1024, "occupancy pad");
         }
 }
