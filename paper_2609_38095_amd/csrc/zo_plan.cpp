@@ -72,7 +72,7 @@ bool groups_aligned(const void* params, uint64_t offset, size_t elem) {
 // 16.3, 1.3 M 19.3 / 17.1; 24 groups, 2.6 M 41.0 / 48.2, 5.1 M 68.0 / 50.5.
 uint64_t any_alignment_from(size_t elem, const Sweep& w) {
   const uint64_t groups = w.update ? w.n_groups : 1;
-  if (elem == 2) return (3 + std::min<uint64_t>(groups, 17)) << 18;
+  if (elem == 2) return std::min<uint64_t>(3 + groups + groups / 4, 20) << 18;
   return groups <= 2 ? 1ull << 18 : groups <= 16 ? 1ull << 20 : 1ull << 22;
 }
 
@@ -156,25 +156,32 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 //     1,374). 768 threads with one group ahead were 13% faster than 1024 on zero weights run
 //     back to back and 2.5% slower (1,590 against 1,550 us) on ordinary ones;
 //   update, nine to sixteen bf16 groups: the first eight groups as above, the others on shared
-//     tables behind them, 1024 threads up to twelve groups, else 768 (1.3 G weights: K = 72 2,343 ->
-//     2,019 us, K = 96 2,873 -> 2,259, K = 128 3,764 -> 3,414; K = 128 with 1024 threads spills
-//     registers: 3,599). Bound by VALU and the LDS together: 16-copy tables for all would need
-//     more than the LDS holds, shared tables for all take 6.3 LDS cycles a read (K = 96 with the
-//     count fixed: 2,630 us);
+//     tables behind them, 1024 threads up to twelve groups, else 768 (1.36 G weights, against shared tables, a
+//     run-time count and 4 KiB chunks: K = 69 2,414 -> 1,781 us, K = 93 3,010 -> 2,470, K = 125 3,865 -> 3,430;
+//     K = 128 with 1024 threads spills registers, 5% slower). Bound by the LDS and VALU together: 16-copy
+//     tables for all would need more than the LDS holds, shared tables for all take 6.3 LDS cycles a read
+//     (K = 96 on 1.3 G weights with the count fixed: 2,630 against 2,260 us);
 //   fp32 updates: one workgroup per CU, 32-copy tables for one and two groups, shared ones for three
-//     (the count fixed at compile time: 2,607 -> 1,630 us); four: 16-copy tables, two workgroups per CU (K = 32: 1,697 -> 1,647 us); five to eight:
+//     (the count fixed at compile time: 2,607 -> 1,630 us); four: 16-copy tables, two workgroups per CU
+//     (1.3 G weights, K = 32: 1,697 against 1,647 us, in two other runs equal to 3% apart); five to eight:
 //     512 threads sharing 16-copy tables (1.3 G weights: K = 40 1,911 -> 1,725 us, K = 48 2,128 ->
 //     1,836, K = 56 2,161 -> 2,001, K = 64 2,169 -> 2,069; 768 and 1024 threads spill registers).
 // An update with a restore probe inside its groups (Algorithm 1's schedule) is the plain
 // update with that group's table changed, and takes the update's shape. Other updates (more than
-// sixteen bf16 groups, or more than eight in fp32, and a restore probe outside the update's groups) are bound by the generator or the LDS table lookups and keep 4 KiB
-// chunks at full occupancy, as do perturbs smaller than the 256 MiB Infinity Cache (updates
-// of such buffers take 8 KiB chunks at full occupancy). Grids: up to
+// sixteen bf16 groups, or more than eight in fp32, and a restore probe outside the update's groups) are bound
+// by the generator or the LDS table lookups and keep 4 KiB chunks at full occupancy. fp32 above eight groups:
+// 512 threads on 16-copy tables for the first eight are faster on small buffers only (12 groups, 0.3 GB 276 ->
+// 225 us, 2.7 GB 1,620 -> 1,772). Above sixteen groups, beyond the 60 to 96 probes that steps are known to
+// use, the count stays a run-time one: a third run needs the full compensation, and a fixed count is
+// twelve more kernels (trial kernels for 24 groups of 1.36 G bf16 weights 5,777 -> 5,567 us). Perturbs
+// smaller than the 256 MiB Infinity Cache take 4 KiB chunks at full occupancy too, updates
+// of such buffers 8 KiB ones. Grids: up to
 // kDefaultMaxBlocks workgroups, grid-stride beyond (in-order dispatch of many short-lived
 // workgroups keeps the streams compact; a persistent grid of one workgroup per CU measured
 // 5.6 TB/s), except where a number of chunks per stream is given: the bf16 perturb of one
-// probe or of two in one probe group, the two-probe fp32 perturb and the bf16 updates of one
-// or two groups run one chunk per stream (OPT-13B: the perturb 6.48 -> 6.67 TB/s, OPT-30B
+// probe or of two in one probe group, the fp32 perturbs, the bf16 updates of one, two and four
+// groups and of five and more, and the fp32 updates of five to eight. One chunk per stream (OPT-13B: the
+// perturb 6.48 -> 6.67 TB/s, OPT-30B
 // 6.20 -> 6.60; two probes in one group +1%, across two groups -0.3%, so those stay
 // grid-stride; 3 G fp32 weights: the two-probe perturb 6.30 -> 6.48 across two probe groups).
 // Four chunks per stream (each workgroup's table build serves four times the bytes) where they take no
@@ -183,7 +190,7 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 // fill their last round), and one started for a few last workgroups lasts as long as a full one. bf16, four
 // chunks against one: eight groups at 0.94 GB (2 rounds for 8) 578 against 601 us, at 1.08 GB (3 for 9)
 // 900 against 700, at 2.63 GB (5 for 20) 1,526 against 1,578; sixteen groups at 0.82 GB (3 for 9) 1,462
-// against 1,146. fp32, eight groups, at 0.54 GB (3 for 9) 280 against 242, at 1.78 GB (7 for 27) 713
+// against 1,146. Five to seven fp32 groups run one always. fp32, eight groups, at 0.54 GB (3 for 9) 280 against 242, at 1.78 GB (7 for 27) 713
 // against 765.
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   const uint64_t group_bytes = kGroupElems * elem;
@@ -245,11 +252,11 @@ Shape list_shape(uint64_t call_elements, uint64_t launch_elements, size_t elem, 
   return sh;
 }
 
-// Dynamic LDS that, with `static_lds` bytes of the kernel's own, admits exactly `cap`
+// Dynamic LDS that, with `static_lds` bytes of the kernel's own, admits exactly `cap` (one or two)
 // workgroups on a CU's 160 KiB (0: no cap).
 size_t occupancy_lds(uint32_t cap, size_t static_lds) {
   if (cap == 0) return 0;
-  const size_t per_block = cap == 1 ? 96 * 1024 : cap == 2 ? 72 * 1024 : cap == 3 ? 48 * 1024 : 36 * 1024;
+  const size_t per_block = cap == 1 ? 96 * 1024 : 72 * 1024;
   return per_block > static_lds ? per_block - static_lds : 0;
 }
 

@@ -94,7 +94,7 @@ struct Sweep {
 // The launch shape of a sweep.
 struct Shape {
   uint32_t chunk_groups;
-  uint32_t blocks_per_cu;    // 0: no cap
+  uint32_t blocks_per_cu;    // at most, one or two; 0: no cap
   uint32_t chunks_per_wave;  // 0: up to kDefaultMaxBlocks workgroups, grid-stride beyond
   uint32_t block = kBlock;   // threads per workgroup
   uint32_t wps = 1;          // waves per stream (per chunk)

@@ -38,7 +38,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // instruction whatever its alignment (the target's unaligned access mode). A shard of 438.6 M
 // bf16 weights starting at an odd global index (K = 16 update) takes 348 us (5.04 TB/s; 6.5 for
 // a shard whose vectors are 16-byte aligned) against 1,875 us on the element-wise path. Bound by
-// the memory pipe: every 1 KiB row touches one cache line more than it holds. Ordinary stores
+// the memory pipe, which takes vectors that are only 2-byte aligned at a lower rate: 4-byte aligned
+// ones, whose 1 KiB rows touch the same extra cache line, take 289 us. Ordinary stores
 // (361 us), or ordinary loads and stores (363 us), are slower there too.
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 

@@ -475,6 +475,7 @@ __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uin
 }
 
 // ---------------------------------------------------------------------------------------
+#if ZO_HAS_PART(0)
 __global__ __launch_bounds__(kBlock) void gen_bits_kernel(uint8_t* out, uint64_t tile_begin, uint64_t n_tiles,
                                                          uint32_t group, Gen gen) {
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
@@ -483,6 +484,7 @@ __global__ __launch_bounds__(kBlock) void gen_bits_kernel(uint8_t* out, uint64_t
     *reinterpret_cast<u32x4*>(out + 16 * i) = u32x4{r.x, r.y, r.z, r.w};
   }
 }
+#endif
 
 // ---------------------------------------------------------------------------------------
 // Host side.
@@ -536,10 +538,10 @@ void launch_update(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Sha
   // A count fixed at compile time: on the spread tables spread_dims gives it where the shape asks for them,
   // else on shared ones. Streaming bf16 updates of one and two groups are paced at four outstanding memory
   // operations, as the one-probe perturb. Two row groups are in flight with one, two and four groups and with
-  // spread tables, one otherwise and where two would spill registers (bf16 above eight groups, fp32 above two).
-  // The fixed count makes each table's
-  // offset an immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and
-  // lets the compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU
+  // spread tables, one otherwise and with spread tables of more groups than leave registers for two (bf16
+  // eight, fp32 two). The fixed count makes each table's offset an immediate of the LDS read, one VALU
+  // instruction fewer per lookup than the run-time loop, and lets the compiler overlap the groups'
+  // generator chains: on cache-sized buffers, bound by VALU
   // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
   // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7. Odd counts have kernels of their
   // own too: run with a zero table as the next even one, K = 72 took 70.7 us there against 62.0, and on 100
