@@ -150,7 +150,19 @@ static void check_kernels() {
     }
 }
 
+// The buffers with which the GPU tests mean to reach four chunks per stream do.
+static void check_test_sizes() {
+  const struct {
+    size_t elem;
+    uint64_t mib;
+    uint32_t groups;
+  } tests[] = {{2, 1000, 6}, {2, 1000, 12}, {2, 1100, 16}, {4, 1000, 8}};
+  for (auto& t : tests)
+    CHECK(shape_for((t.mib << 20) / t.elem - 77, t.elem, update_of(t.groups)).chunks_per_wave == 4, "%u groups", t.groups);
+}
+
 int main() {
+  check_test_sizes();
   check_kernels();
   check_lists();
   check_misaligned();

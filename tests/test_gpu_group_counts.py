@@ -7,27 +7,15 @@ import torch
 
 import oracle
 import paper_2609_38095_amd as zo
+import streaming
 
 SEED, STEP, OFFSET = 0x1234_5678_9ABC, 7, 3
 LR, EPS = 1e-3, 1e-3
-# 256 MiB and a ragged tail: the whole call streams, each half of it does not
-N = {"bf16": 2 ** 27 + 4099, "f32": 2 ** 26 + 4099}
-TORCH = {"bf16": torch.bfloat16, "f32": torch.float32}
 
 
 @pytest.fixture(scope="module", params=["bf16", "f32"])
 def theta(request):
-    g = torch.Generator(device="cuda").manual_seed(1)
-    return request.param, torch.empty(N[request.param], device="cuda", dtype=TORCH[request.param]).normal_(
-        0.0, 0.02, generator=g)
-
-
-def _host(t, dtype):
-    return t.cpu().numpy() if dtype == "f32" else t.view(torch.int16).cpu().numpy().view(np.uint16)
-
-
-def _windows(n):
-    return [(0, 1500), (n // 2 - 700, 1400), (n - 1500, 1500)]
+    return request.param, streaming.weights(request.param)
 
 
 @pytest.mark.gpu
@@ -53,14 +41,14 @@ def test_update_of_every_group_count(theta, groups, restore):
     call(halves[m:], OFFSET + m)
     bits = torch.int16 if dtype == "bf16" else torch.int32
     assert torch.equal(whole.view(bits), halves.view(bits))
-    for at, ln in _windows(n):
-        th = _host(base[at:at + ln], dtype)
+    for at, ln in streaming.windows(n):
+        th = streaming.host(base[at:at + ln], dtype)
         if restore:
             want = oracle.update_restore(th, dtype, OFFSET + at, SEED, STEP, c, LR, K - 1, EPS)
         else:
             want = oracle.update(th, dtype, OFFSET + at, SEED, STEP, c, LR)
         w64, g64 = (x.astype(np.float64) if dtype == "f32" else oracle.bf16_to_f64(x)
-                    for x in (want, _host(whole[at:at + ln], dtype)))
+                    for x in (want, streaming.host(whole[at:at + ln], dtype)))
         # 1e-6 of max(|theta|, lr sum |c| and the restore), and for bf16 one neighbouring value
         scale = LR * np.abs(c.astype(np.float64)).sum() + (EPS if restore else 0.0)
         allow = 1e-6 * np.maximum(np.abs(w64), scale)

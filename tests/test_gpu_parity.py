@@ -137,7 +137,8 @@ def test_perturb_bit_exact(dtype, n, offset, k, eps):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shift,offset", [(1, 1), (1, 0), (3, 0), (5, 12)])
 def test_perturb_unaligned_storage(dtype, shift, offset):
-    """A view starting mid-tile: vector path when (pointer, offset) agree, element path otherwise."""
+    """A view starting mid-tile: row groups when (pointer, offset) agree in alignment, element by element
+    otherwise (a launch this small)."""
     note(f"perturb unaligned {dtype} shift {shift} offset {offset}")
     n = 5000
     if dtype == "f32":
@@ -505,10 +506,9 @@ def test_segments_streaming_shape_equal_flat_bits():
     (tiny ones among multi-million ones, none a multiple of the 32 KiB chunk, the first at a
     global offset of 777) get, in every element, the bits that the single-buffer calls give
     the same values laid out flat: perturb, a two-probe transition, the update and the update
-    with restore at K = 16 (two waves per stream, one chunk per stream), K = 32 (two-plane
-    32-copy tables in 1024-thread workgroups; 16-copy tables at two workgroups per CU) and
-    K = 64 (16-copy tables shared by 1024 or 512 threads). The single-buffer calls are
-    themselves checked against the oracle at full size."""
+    with restore at K = 16 (two waves per stream, one chunk per stream), K = 32 (16-copy tables
+    in 512-thread workgroups, two per CU) and K = 64 (16-copy tables shared by 1024 threads). The
+    single-buffer calls are themselves checked against the oracle at full size."""
     rng = np.random.default_rng(13)
     sizes = [int(x) for x in rng.integers(1, 8_000_000, 50)] + [1, 7, 1023, 1024, 1025, 16_385]
     sizes = [sizes[i] for i in rng.permutation(len(sizes))]
@@ -558,10 +558,11 @@ def test_segments_streaming_shape_equal_flat_bits():
     same("update_restore K=64")
 
 
-@pytest.mark.parametrize("op", ["perturb", "update16", "restore16", "update32", "restore32", "update64", "restore64"])
+@pytest.mark.parametrize("op", ["perturb", "update16", "restore16", "update32", "restore32", "update64", "restore64",
+                                "update24", "update48", "restore72", "update96", "restore128"])
 def test_streaming_results_independent_of_grid(op):
-    """Above the streaming threshold, where the launches use two waves per stream, one or four
-    chunks per stream and 512- or 1024-thread workgroups: capping the grid at 1, 7 or 300
+    """Above the streaming threshold, where the launches use two waves per stream, one chunk per
+    stream and 512-, 768- or 1024-thread workgroups: capping the grid at 1, 7 or 300
     workgroups (every stream then loops over many chunks) leaves every bit of the result as
     the default grid gives it."""
     n = 144_000_019
@@ -570,7 +571,7 @@ def test_streaming_results_independent_of_grid(op):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(21)
     src.normal_(0.0, 0.02, generator=gen)
-    c = np.random.default_rng(5).standard_normal(64).astype(np.float32)
+    c = np.random.default_rng(5).standard_normal(128).astype(np.float32)
     outs = []
     try:
         for blocks in (0, 1, 7, 300):
@@ -579,7 +580,7 @@ def test_streaming_results_independent_of_grid(op):
             if op == "perturb":
                 zo.zo_perturb(t, 11, 1e-3, 5, 1, offset=33)
             else:
-                K = int(op[-2:])
+                K = int(op.lstrip("abcdefghijklmnopqrstuvwxyz"))
                 if op.startswith("update"):
                     zo.zo_update_ex(t, c[:K], 1e-3, 5, 1, offset=33)
                 else:

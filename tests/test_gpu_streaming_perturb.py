@@ -6,27 +6,15 @@ import torch
 
 import oracle
 import paper_2609_38095_amd as zo
+import streaming
 
 SEED, STEP, OFFSET = 0x1234_5678_9ABC, 7, 3
 EPS = 1e-3
-# 256 MiB and a ragged tail: the whole call streams, each half of it does not
-N = {"bf16": 2 ** 27 + 4099, "f32": 2 ** 26 + 4099}
-TORCH = {"bf16": torch.bfloat16, "f32": torch.float32}
 
 
 @pytest.fixture(scope="module", params=["bf16", "f32"])
 def theta(request):
-    g = torch.Generator(device="cuda").manual_seed(1)
-    return request.param, torch.empty(N[request.param], device="cuda", dtype=TORCH[request.param]).normal_(
-        0.0, 0.02, generator=g)
-
-
-def _host(t, dtype):
-    return t.cpu().numpy() if dtype == "f32" else t.view(torch.int16).cpu().numpy().view(np.uint16)
-
-
-def _windows(n):
-    return [(0, 1500), (n // 2 - 700, 1400), (n - 1500, 1500)]
+    return request.param, streaming.weights(request.param)
 
 
 @pytest.mark.gpu
@@ -47,9 +35,12 @@ def test_streaming_perturb(theta, two):
     call(halves[:m], OFFSET)
     call(halves[m:], OFFSET + m)
     bits = torch.int16 if dtype == "bf16" else torch.int32
-    assert torch.equal(whole.view(bits), halves.view(bits))
-    if two:
-        return
-    for at, ln in _windows(n):
-        want = oracle.perturb(_host(base[at:at + ln], dtype), dtype, OFFSET + at, SEED, STEP, 5, EPS)
-        np.testing.assert_array_equal(_host(whole[at:at + ln], dtype), want)
+    same = torch.equal(whole.view(bits), halves.view(bits))
+    assert same
+    for at, ln in streaming.windows(n):
+        th = streaming.host(base[at:at + ln], dtype)
+        if two:
+            want = oracle.perturb2(th, dtype, OFFSET + at, SEED, STEP, 7, EPS, 8, -2 * EPS)
+        else:
+            want = oracle.perturb(th, dtype, OFFSET + at, SEED, STEP, 5, EPS)
+        np.testing.assert_array_equal(streaming.host(whole[at:at + ln], dtype), want)

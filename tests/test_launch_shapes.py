@@ -8,7 +8,9 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2609_38095_amd as zo
+import streaming
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2609_38095_amd", "csrc")
@@ -78,3 +80,32 @@ def test_list_updates_equal_flat_ones(lists, groups):
 def test_list_perturbs_equal_flat_ones(lists, k_b, eps_b):
     _check(lists, lambda t, o: zo.zo_perturb2(t, 3, 1e-3, k_b, eps_b, 5, 7, o),
            lambda ts, os_: zo.zo_perturb_segments(ts, os_, 3, 1e-3, k_b, eps_b, 5, 7))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,mib,K", [("bf16", 1000, 48), ("bf16", 1000, 96), ("bf16", 1100, 128), ("f32", 1000, 64)])
+@pytest.mark.parametrize("restore", [False, True])
+def test_four_chunks_per_stream(dtype, mib, K, restore):
+    """Buffers whose flat update walks four chunks per stream: the bits that a list of their parts gives (one
+    chunk per stream), and on windows the oracle's values within the update's bar."""
+    n = (mib << 20) // (2 if dtype == "bf16" else 4) - 77
+    base = streaming.weights(dtype, n)
+    c = np.random.default_rng(K).normal(0, 0.5, K).astype(np.float32)
+    eps, offset = (1e-3, 5) if restore else (0.0, 5)
+    whole, parts = base.clone(), base.clone()
+    zo.zo_update_restore(whole, c, 1e-3, 9, 4, K - 1, eps, offset)
+    at = [0, n // 3, n // 3 + 1025, n]
+    zo.zo_update_segments([parts[a:b] for a, b in zip(at, at[1:])], [offset + a for a in at[:-1]], c, 1e-3, 9, 4, K - 1, eps)
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    same = torch.equal(whole.view(bits), parts.view(bits))
+    assert same
+    for a, ln in streaming.windows(n):
+        th = streaming.host(base[a:a + ln], dtype)
+        want = oracle.update_restore(th, dtype, offset + a, 9, 4, c, 1e-3, K - 1, eps)
+        w64, g64 = (x.astype(np.float64) if dtype == "f32" else oracle.bf16_to_f64(x)
+                    for x in (want, streaming.host(whole[a:a + ln], dtype)))
+        # 1e-6 of max(|theta|, lr sum |c| and the restore), and for bf16 one neighbouring value
+        allow = 1e-6 * np.maximum(np.abs(w64), 1e-3 * np.abs(c.astype(np.float64)).sum() + eps)
+        if dtype == "bf16":
+            allow = allow + np.maximum(np.abs(w64), 2.0 ** -126) * 2.0 ** -7
+        assert np.all(np.abs(g64 - w64) <= allow)
