@@ -168,30 +168,30 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 //     1,836, K = 56 2,161 -> 2,001, K = 64 2,169 -> 2,069; 768 and 1024 threads spill registers).
 // An update with a restore probe inside its groups (Algorithm 1's schedule) is the plain
 // update with that group's table changed, and takes the update's shape. Other updates (more than
-// sixteen bf16 groups, or more than eight in fp32, and a restore probe outside the update's groups) are bound
-// by the generator or the LDS table lookups and keep 4 KiB chunks at full occupancy. fp32 above eight groups:
-// 512 threads on 16-copy tables for the first eight are faster on small buffers only (12 groups, 0.3 GB 276 ->
-// 225 us, 2.7 GB 1,620 -> 1,772). Above sixteen groups, beyond the 60 to 96 probes that steps are known to
-// use, the count stays a run-time one: a third run needs the full compensation, and a fixed count is
-// twelve more kernels (trial kernels for 24 groups of 1.36 G bf16 weights 5,777 -> 5,567 us). Perturbs
-// smaller than the 256 MiB Infinity Cache take 4 KiB chunks at full occupancy too, updates
-// of such buffers 8 KiB ones. Grids: up to
+// sixteen bf16 groups, or more than eight in fp32, and a restore probe outside the update's groups)
+// are bound by the generator or the LDS table lookups and keep 4 KiB chunks at full occupancy. fp32
+// above eight groups: 512 threads on 16-copy tables for the first eight are faster on small buffers
+// only (12 groups, 0.3 GB 276 -> 225 us, 2.7 GB 1,620 -> 1,772). Above sixteen groups, beyond the 60
+// to 96 probes that steps are known to use, the count stays a run-time one: a third run needs the full
+// compensation, and a fixed count is twelve more kernels (trial kernels for 24 groups of 1.36 G bf16
+// weights 5,777 -> 5,567 us). Perturbs smaller than the 256 MiB Infinity Cache take 4 KiB chunks at
+// full occupancy too, updates of such buffers 8 KiB ones. Grids: up to
 // kDefaultMaxBlocks workgroups, grid-stride beyond (in-order dispatch of many short-lived
 // workgroups keeps the streams compact; a persistent grid of one workgroup per CU measured
 // 5.6 TB/s), except where a number of chunks per stream is given: the bf16 perturb of one
 // probe or of two in one probe group, the fp32 perturbs, the bf16 updates of one, two and four
-// groups and of five and more, and the fp32 updates of five to eight. One chunk per stream (OPT-13B: the
-// perturb 6.48 -> 6.67 TB/s, OPT-30B
-// 6.20 -> 6.60; two probes in one group +1%, across two groups -0.3%, so those stay
-// grid-stride; 3 G fp32 weights: the two-probe perturb 6.30 -> 6.48 across two probe groups).
+// groups and of five and more, and the fp32 updates of five to eight. One chunk per stream: OPT-13B,
+// the perturb 6.48 -> 6.67 TB/s, OPT-30B 6.20 -> 6.60; two probes in one group +1%, across two groups
+// -0.3%, so those stay grid-stride; 3 G fp32 weights, the two-probe perturb 6.30 -> 6.48 across two
+// probe groups.
 // Four chunks per stream (each workgroup's table build serves four times the bytes) where they take no
 // longer, counted in rounds of one workgroup on each of the 256 CUs: a round of four chunks lasts as
 // long as four rounds of one, less the table builds (2% of it in bf16, 10% in fp32, measured where both
 // fill their last round), and one started for a few last workgroups lasts as long as a full one. bf16, four
 // chunks against one: eight groups at 0.94 GB (2 rounds for 8) 578 against 601 us, at 1.08 GB (3 for 9)
 // 900 against 700, at 2.63 GB (5 for 20) 1,526 against 1,578; sixteen groups at 0.82 GB (3 for 9) 1,462
-// against 1,146. Five to seven fp32 groups run one always. fp32, eight groups, at 0.54 GB (3 for 9) 280 against 242, at 1.78 GB (7 for 27) 713
-// against 765.
+// against 1,146. fp32, eight groups, at 0.54 GB (3 for 9) 280 against 242, at 1.78 GB (7 for 27) 713
+// against 765; five to seven groups run one always.
 Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
   const uint64_t group_bytes = kGroupElems * elem;
   if (elements * elem < kStreamBytes) {
@@ -244,7 +244,8 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
 // of each other either way; of 533 MiB (2.6 GB, bf16, K = 96) the streaming one takes 2,659 us, the
 // other 2,751.
 Shape list_shape(uint64_t call_elements, uint64_t launch_elements, size_t elem, const Sweep& w) {
-  const bool large_blocks = w.update && !(w.restore && !w.fold) && w.n_groups >= 5 && spread_dims(elem, w.n_groups).copies;
+  const bool large_blocks = w.update && !(w.restore && !w.fold) && w.n_groups >= 5 &&
+                            spread_dims(elem, w.n_groups).copies;
   if (large_blocks && call_elements * elem >= kStreamBytes && launch_elements * elem < kStreamBytes)
     return launch_elements * elem < kShortLaunchBytes ? short_chunks(elem) : shape_for(launch_elements, elem, w);
   Shape sh = shape_for(call_elements, elem, w);

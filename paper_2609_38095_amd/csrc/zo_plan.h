@@ -22,7 +22,7 @@ constexpr uint32_t kCUs = 256;
 constexpr uint32_t kSegsPerLaunch = 64;            // segments per batched launch (kernel arguments, ~5 KiB)
 constexpr uint64_t kMaxLaunchChunks = 1ull << 31;  // chunks per launch: 32-bit indices with room for the stride
 constexpr uint64_t kStreamBytes = 256ull << 20;    // sweeps at least this large stream (above the Infinity Cache)
-constexpr uint64_t kShortLaunchBytes = 32ull << 20;  // launches of a list call below this take 4 KiB chunks (list_shape)
+constexpr uint64_t kShortLaunchBytes = 32ull << 20;  // smaller launches of a list: 4 KiB chunks (list_shape)
 
 // One segment: global elements [lo, hi) stored from `base` (the address of global element lo).
 // The `span` full row groups from global group g_lo (stored from `gbase`) take the vector
@@ -36,8 +36,7 @@ constexpr uint64_t kShortLaunchBytes = 32ull << 20;  // launches of a list call 
 // workgroups' 128 KiB blocks aligned, 8.0-8.25 ms shifted by one to three 32 KiB chunks). The
 // edge tiles [head_t0, +head_nt) and [tail_t0, +tail_nt) (fewer than 1024 elements at each
 // end; all of a misaligned tensor in a small launch, see any_alignment_from) take the element-wise
-// path. The kernels walk chunks and groups with
-// 32-bit indices relative to the segment (compares of 64-bit indices need a vector register
+// path. The kernels walk chunks and groups with 32-bit indices relative to the segment (compares of 64-bit indices need a vector register
 // on gfx950, and writing one that a pending store still reads makes the wave wait for that
 // store); a segment stays below 2^30 row groups (n < ZO_N_MAX) and a launch below 2^31 chunks.
 struct Plan {
@@ -101,9 +100,10 @@ struct Shape {
   uint32_t copies = 0;       // update: copies of each spread table (0: shared tables)
 };
 
-// The kernel of a streaming update on spread tables, by weight type and probe groups: copies of each table
-// (0: there is none, the count runs on shared tables), threads per workgroup and waves per stream. The
-// planner and the kernels' dispatch both take it from here.
+// The kernel of a streaming update on spread tables, by weight type and probe groups: copies of each
+// table (0: there is none, the count runs on shared tables; one bf16 group's leaves the LDS half idle),
+// threads per workgroup and waves per stream. The planner and the kernels' dispatch both take it from
+// here; shape_for says why each.
 struct SpreadDims {
   uint32_t copies, block, wps;
 };

@@ -217,6 +217,12 @@ template <int C>
 constexpr uint32_t groups_per_plane() {
   return C > 0 ? 64 / C : 1;
 }
+// Whether group g's table is spread. Up to eight groups it takes no look at g, which would leave code for
+// shared tables in kernels that have none (80 of the two-group update's 6,915 instructions).
+template <int NG, int C>
+__device__ __forceinline__ bool is_spread(uint32_t g) {
+  return C > 0 && (NG <= static_cast<int>(kSpreadGroups) || g < kSpreadGroups);
+}
 template <int NG, int C>
 __device__ __forceinline__ float* shared_table(float* tab, uint32_t g) {
   return tab + shared_base(NG, C) + 256u * (g - spread_groups(NG, C));
@@ -233,9 +239,9 @@ __device__ __forceinline__ float* shared_table(float* tab, uint32_t g) {
 // and the coefficient reads are uniform (scalar loads), and the sign of slot s is an XOR of the
 // coefficient's sign bit with bit s of ~b. A workgroup of BLOCK threads builds BLOCK / 256
 // groups at a time: thread b + 256 m writes entry b of groups m, m + BLOCK / 256, ... The count is a
-// constant of the loop from three groups on (with the run-time one, K = 64 and 96 on 270 M bf16 weights
-// take 445 and 710 us against 377 and 582); with one group, unrolling the loop away slows the streaming fp32
-// update (K = 5, 5.2 GB: 1,601 -> 1,693 us), with two it costs fp32 0 to 2%.
+// constant of the loop from three groups on (with the run-time one, K = 64 and 96 on 270 M bf16
+// weights take 445 and 710 us against 377 and 582); with one group, unrolling the loop away slows the
+// streaming fp32 update (K = 5, 5.2 GB: 1,601 -> 1,693 us), with two it costs fp32 0 to 2%.
 template <int NG, int C, int BLOCK>
 __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32_t k_base, uint32_t K,
                                              uint32_t n_groups, float lr, uint32_t fold_g, const Probe& fold) {
@@ -255,7 +261,7 @@ __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32
     }
     float t = (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) * lr;
     if (g == fold_g) t = t - delta(fold, b);
-    if (g < spread_groups(NG, C)) {
+    if (is_spread<NG, C>(g)) {
       // entry b's C / 4 float4 of copies, 256 bytes after entry b - 1's: thread b writes them
       // starting at float4 b mod (C / 4), so that the lanes of each write spread over the banks
       // the group's copies occupy (in a fixed order all 64 would land on the same 4 banks)
@@ -394,7 +400,7 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], float* tab, const
       for (int j = 0; j < (int)kTile; ++j) {
         const uint32_t byte = word_byte(x[j >> 2], j & 3);
         float v;
-        if (g < spread_groups(NG, C)) {
+        if (is_spread<NG, C>(g)) {
           constexpr uint32_t P = groups_per_plane<C>();
           v = tab[kSpreadFloats * (g / P) + 64u * byte + C * (g % P) + (threadIdx.x % (C > 0 ? C : 1))];
         } else {
@@ -424,14 +430,15 @@ __device__ __forceinline__ void tile_sums(float (&acc)[kTile], float* tab, const
 // is folded into that group's table (see build_tables), so the per-element work is the plain
 // update's; kPerElement, r lies outside them and is applied per element as t =
 // fl(theta + delta_r), then t minus the sum of the table values, its generator words made
-// after the group loop. Each is a kernel of its own: asked for at run time, the fold costs every table
-// build 40 to 60 ns a group (K = 133 on 100 weights: 18.1 -> 18.8 us, in fp32 17.8 -> 18.9).
+// after the group loop. Each is a kernel of its own: asked for at run time, the fold costs every
+// table build 40 to 60 ns a group (K = 133 on 100 weights: 18.1 -> 18.8 us, in fp32 17.8 -> 18.9).
 enum RestoreMode { kNoRestore = 0, kFolded = 1, kPerElement = 2 };
 
 template <class S, int NG, int RESTORE, int N, int C, int BLOCK, int WPS, int PACE, int AHEAD>
 __global__ __launch_bounds__(BLOCK) void update_kernel(Plans<N> ps, Gen gen, uint32_t k_base, uint32_t K,
                                                       uint32_t n_groups, Coefs cf, float lr, Probe r) {
-  static_assert(C == 0 || ((C == 16 || C == 32) && spread_groups(NG, C) * C <= 128), "spread tables fill at most two planes");
+  static_assert(C == 0 || ((C == 16 || C == 32) && spread_groups(NG, C) * C <= 128),
+                "spread tables fill at most two planes");
   // n_groups x 256 floats (C > 0: the interleaved copies): static for a fixed group count
   // (constant LDS offsets), else dynamic.
   extern __shared__ float tab_dyn[];
@@ -535,24 +542,25 @@ namespace zo {
 template <class S, int N, int MODE>
 void launch_update(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shape& sh, hipStream_t st) {
   constexpr bool bf16 = sizeof(typename S::storage) == 2;
-  // A count fixed at compile time: on the spread tables spread_dims gives it where the shape asks for them,
-  // else on shared ones. Streaming bf16 updates of one and two groups are paced at four outstanding memory
-  // operations, as the one-probe perturb. Two row groups are in flight with one, two and four groups and with
-  // spread tables, one otherwise and with spread tables of more groups than leave registers for two (bf16
-  // eight, fp32 two). The fixed count makes each table's offset an immediate of the LDS read, one VALU
-  // instruction fewer per lookup than the run-time loop, and lets the compiler overlap the groups'
-  // generator chains: on cache-sized buffers, bound by VALU
-  // and the LDS, 30 M weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and
-  // 105.1 -> 84.5 at K = 96; bf16 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7. Odd counts have kernels of their
-  // own too: run with a zero table as the next even one, K = 72 took 70.7 us there against 62.0, and on 100
-  // weights, where the run-time loop takes 11.4 us, 12.1 against 11.3.
+  // A count fixed at compile time: on the spread tables spread_dims gives it where the shape asks for
+  // them, else on shared ones. bf16 updates of one and (streaming) two groups are paced at four
+  // outstanding memory operations, as the one-probe perturb. Two row groups are in flight with one, two
+  // and four groups and with spread tables, one otherwise and with spread tables of more groups than
+  // leave registers for two (bf16 eight, fp32 two). The fixed count makes each table's offset an
+  // immediate of the LDS read, one VALU instruction fewer per lookup than the run-time loop, and lets the
+  // compiler overlap the groups' generator chains: on cache-sized buffers, bound by VALU and the LDS, 30 M
+  // weights take, fp32, 45.1 -> 43.5 us at K = 24, 59.9 -> 52.2 at K = 48 and 105.1 -> 84.5 at K = 96; bf16
+  // 28.1 -> 25.3, 45.9 -> 41.8 and 85.8 -> 79.7. Odd counts have kernels of their own too: run with a zero
+  // table as the next even one, K = 69 took 69.9 us there against 62.0, and on 100 weights, where the
+  // run-time loop takes 11.4 us, 12.1 against 11.3.
   auto fixed = [&](auto groups) {
     constexpr int NG = decltype(groups)::value;
     constexpr SpreadDims d = spread_dims(sizeof(typename S::storage), NG);
     if constexpr (d.copies > 0) {
       constexpr int kAhead = NG <= 2 || (bf16 && NG <= 8) ? 2 : 1;
       if (sh.copies)
-        return launch_kernel<S, NG, MODE, N, d.copies, d.block, d.wps, bf16 && NG == 2 ? 4 : 0, kAhead>(ps, gen, w, sh, st);
+        return launch_kernel<S, NG, MODE, N, d.copies, d.block, d.wps, bf16 && NG == 2 ? 4 : 0, kAhead>(ps, gen, w,
+                                                                                                        sh, st);
     }
     constexpr int kAhead = NG == 1 || NG == 2 || NG == 4 ? 2 : 1;
     launch_kernel<S, NG, MODE, N, 0, kBlock, 1, bf16 && NG == 1 ? 4 : 0, kAhead>(ps, gen, w, sh, st);
