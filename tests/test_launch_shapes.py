@@ -62,17 +62,35 @@ def _check(lists, flat_call, list_call):
     differ = [i for i, (t, a, s) in enumerate(zip(ts, starts, sizes))
               if not torch.equal(t.view(bits), whole[a:a + s].view(bits))]
     assert differ == []
+    return whole, base
+
+
+def _check_windows(base, whole, offset, c, k_restore, eps, k_base=0):
+    """The update's values on windows of a flat result against the oracle, within the update's bar."""
+    dtype = "bf16" if base.dtype == torch.bfloat16 else "f32"
+    for a, ln in streaming.windows(base.numel()):
+        th = streaming.host(base[a:a + ln], dtype)
+        want = oracle.update_restore(th, dtype, offset + a, 5, 7, c, 1e-3, k_restore, eps, k_base=k_base)
+        w64, g64 = (x.astype(np.float64) if dtype == "f32" else oracle.bf16_to_f64(x)
+                    for x in (want, streaming.host(whole[a:a + ln], dtype)))
+        # 1e-6 of max(|theta|, lr sum |c| and the restore), and for bf16 one neighbouring value
+        allow = 1e-6 * np.maximum(np.abs(w64), 1e-3 * np.abs(c.astype(np.float64)).sum() + abs(eps))
+        if dtype == "bf16":
+            allow = allow + np.maximum(np.abs(w64), 2.0 ** -126) * 2.0 ** -7
+        assert np.all(np.abs(g64 - w64) <= allow)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("groups", list(range(1, 18)))
 def test_list_updates_equal_flat_ones(lists, groups):
-    """Bit for bit, with k_base inside a group and a restore in the first group (even counts) or none."""
+    """Bit for bit, with k_base inside a group and a restore in the first group (even counts) or none; the flat
+    one within the update's bar of the oracle."""
     K, k_base = 8 * groups - 5, 3
     c = np.random.default_rng(groups).normal(0, 0.5, K).astype(np.float32)
     eps = 1e-3 if groups % 2 == 0 else 0.0
-    _check(lists, lambda t, o: zo.zo_update_restore(t, c, 1e-3, 5, 7, 4, eps, o, k_base),
-           lambda ts, os_: zo.zo_update_segments(ts, os_, c, 1e-3, 5, 7, 4, eps, k_base))
+    whole, offset = _check(lists, lambda t, o: zo.zo_update_restore(t, c, 1e-3, 5, 7, 4, eps, o, k_base),
+                           lambda ts, os_: zo.zo_update_segments(ts, os_, c, 1e-3, 5, 7, 4, eps, k_base))
+    _check_windows(lists[0], whole, offset, c, 4, eps, k_base)
 
 
 @pytest.mark.gpu
@@ -93,19 +111,10 @@ def test_four_chunks_per_stream(dtype, mib, K, restore):
     c = np.random.default_rng(K).normal(0, 0.5, K).astype(np.float32)
     eps, offset = (1e-3, 5) if restore else (0.0, 5)
     whole, parts = base.clone(), base.clone()
-    zo.zo_update_restore(whole, c, 1e-3, 9, 4, K - 1, eps, offset)
+    zo.zo_update_restore(whole, c, 1e-3, 5, 7, K - 1, eps, offset)
     at = [0, n // 3, n // 3 + 1025, n]
-    zo.zo_update_segments([parts[a:b] for a, b in zip(at, at[1:])], [offset + a for a in at[:-1]], c, 1e-3, 9, 4, K - 1, eps)
+    zo.zo_update_segments([parts[a:b] for a, b in zip(at, at[1:])], [offset + a for a in at[:-1]], c, 1e-3, 5, 7, K - 1, eps)
     bits = torch.int16 if dtype == "bf16" else torch.int32
     same = torch.equal(whole.view(bits), parts.view(bits))
     assert same
-    for a, ln in streaming.windows(n):
-        th = streaming.host(base[a:a + ln], dtype)
-        want = oracle.update_restore(th, dtype, offset + a, 9, 4, c, 1e-3, K - 1, eps)
-        w64, g64 = (x.astype(np.float64) if dtype == "f32" else oracle.bf16_to_f64(x)
-                    for x in (want, streaming.host(whole[a:a + ln], dtype)))
-        # 1e-6 of max(|theta|, lr sum |c| and the restore), and for bf16 one neighbouring value
-        allow = 1e-6 * np.maximum(np.abs(w64), 1e-3 * np.abs(c.astype(np.float64)).sum() + eps)
-        if dtype == "bf16":
-            allow = allow + np.maximum(np.abs(w64), 2.0 ** -126) * 2.0 ** -7
-        assert np.all(np.abs(g64 - w64) <= allow)
+    _check_windows(base, whole, offset, c, K - 1, eps)
