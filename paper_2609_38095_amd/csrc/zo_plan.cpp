@@ -191,8 +191,10 @@ Gen make_gen(uint64_t seed, uint32_t step) {
 // chunks against one: eight groups at 0.94 GB (2 rounds for 8) 578 against 601 us, at 1.08 GB (3 for 9)
 // 900 against 700, at 2.63 GB (5 for 20) 1,526 against 1,578; sixteen groups at 0.82 GB (3 for 9) 1,462
 // against 1,146. fp32, eight groups, at 0.54 GB (3 for 9) 280 against 242, at 1.78 GB (7 for 27) 713
-// against 765; five to seven groups run one always.
-Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
+// against 765; five to seven groups run one always. Workgroups are counted as memory blocks touched from
+// `addr`, the buffer's address: 0.40 GB in whole blocks are 3 rounds of one chunk (173 us at K = 40) or one of
+// four (212), the same bytes across one more block 4 and 1.
+Shape shape_for(uint64_t elements, size_t elem, const Sweep& w, uintptr_t addr) {
   const uint64_t group_bytes = kGroupElems * elem;
   if (elements * elem < kStreamBytes) {
     if (!w.update) return short_chunks(elem);
@@ -223,11 +225,10 @@ Shape shape_for(uint64_t elements, size_t elem, const Sweep& w) {
     if (elem == 2 && g != 3) sh.chunks_per_wave = 1;
     return sh;
   }
-  auto rounds = [&](uint64_t chunks) {  // memory may cut one workgroup's block off the first
-    return ceil_div(elements * elem / (chunks * kMaxChunkBytes * (sh.block / 64)) + 1, kCUs);
-  };
-  const bool four = (elem == 2 || g == 8) && 400 * rounds(4) <= (elem == 2 ? 102 : 110) * rounds(1);
-  sh.chunks_per_wave = four ? 4 : 1;
+  const uint64_t bytes = kMaxChunkBytes * (sh.block / 64);  // a workgroup's aligned block, one chunk per stream
+  const uint64_t blocks = (addr % bytes + elements * elem + bytes - 1) / bytes;
+  const uint64_t one = ceil_div(blocks, kCUs), four = ceil_div(ceil_div(blocks, 4), kCUs);
+  sh.chunks_per_wave = (elem == 2 || g == 8) && 400 * four <= (elem == 2 ? 102 : 110) * one ? 4 : 1;
   return sh;
 }
 

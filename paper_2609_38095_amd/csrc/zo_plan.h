@@ -156,7 +156,7 @@ Plan make_plan(void* params, uint64_t offset, uint64_t n, size_t elem, uint32_t 
                bool any_alignment = true);
 uint32_t plan_chunks(const Plan& pl, uint32_t chunk_groups);
 uint32_t grid_for(uint64_t work_items, uint64_t per_block, uint32_t block, bool sized = false);
-Shape shape_for(uint64_t elements, size_t elem, const Sweep& w);
+Shape shape_for(uint64_t elements, size_t elem, const Sweep& w, uintptr_t addr = 0);
 Shape list_shape(uint64_t call_elements, uint64_t launch_elements, size_t elem, const Sweep& w);
 size_t occupancy_lds(uint32_t cap, size_t static_lds);
 void set_max_blocks(uint32_t max_blocks);

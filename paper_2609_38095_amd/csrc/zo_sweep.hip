@@ -669,7 +669,7 @@ void launch_sweep(const Plans<N>& ps, const Gen& gen, const Sweep& w, const Shap
 // One contiguous tensor.
 template <class S>
 int run_one(void* params, uint64_t offset, uint64_t n, uint64_t seed, uint32_t step, const Sweep& w, void* stream) {
-  const Shape sh = shape_for(n, sizeof(typename S::storage), w);
+  const Shape sh = shape_for(n, sizeof(typename S::storage), w, reinterpret_cast<uintptr_t>(params));
   const Gen gen = make_gen(seed, step);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const zo_segment seg{params, offset, n};
