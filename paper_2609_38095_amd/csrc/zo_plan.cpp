@@ -65,15 +65,17 @@ bool groups_aligned(const void* params, uint64_t offset, size_t elem) {
 // From how many weights of a launch on its misaligned tensors (groups_aligned false) take full row
 // groups. Smaller launches are bound by the latency of one wave: a tile per lane and nothing after it
 // is shorter than a chunk of row groups followed by the head and tail tiles, the more so the more
-// probe groups; larger ones by the element-wise path's 2-byte or 4-byte accesses. Flat calls at an odd
-// address, element-wise against row groups, us: bf16, one group, 0.9 M weights 7.8 / 7.8, 1.3 M 9.9 / 8.8;
-// 8 groups, 40 thousand 12.3 / 19.5, 2.6 M 19.3 / 20.7, 3.6 M 22.5 / 20.7; 17 groups, 40 thousand 20.6 /
-// 40.3, 3.6 M 32.9 / 41.5, 5.1 M 47.7 / 44.2; fp32, one probe, 240 thousand 6.7 / 6.4; 8 groups, 0.9 M 14.0 /
-// 16.3, 1.3 M 19.3 / 17.1; 24 groups, 2.6 M 41.0 / 48.2, 5.1 M 68.0 / 50.5.
+// probe groups. The element-wise path's time rises in steps of 2^20 weights (one workgroup more on each
+// CU), so the lines lie there. Flat calls at an odd address with both ends ragged, element-wise against row
+// groups, us: bf16, 3 groups, 0.9 M weights 9.7 / 11.3, 1.3 M 12.3 / 12.1; 4 groups, 1.8 M 12.8 / 13.8, 2.6 M
+// 16.0 / 14.2; 8 groups, 40 thousand 12.3 / 19.5, 2.6 M 19.3 / 20.7, 3.6 M 22.5 / 20.7; 17 groups, 40 thousand
+// 20.6 / 40.3, 3.6 M 32.9 / 41.5, 5.1 M 47.7 / 44.2; fp32, one probe, 80 thousand 6.4 / 6.5 (6.7 / 5.1 from
+// a row group's start on); 2 groups, 160 thousand 8.3 / 9.2, 320 thousand 8.8 / 8.6; 8 groups, 0.9 M 14.0 / 16.3,
+// 1.3 M 19.3 / 17.1; 24 groups, 2.6 M 41.0 / 48.2, 3.6 M 47.0 / 48.4, 5.1 M 68.0 / 50.5.
 uint64_t any_alignment_from(size_t elem, const Sweep& w) {
   const uint64_t groups = w.update ? w.n_groups : 1;
-  if (elem == 2) return std::min<uint64_t>(3 + groups + groups / 4, 20) << 18;
-  return groups <= 2 ? 1ull << 18 : groups <= 16 ? 1ull << 20 : 1ull << 22;
+  if (elem == 2) return std::min<uint64_t>(1 + groups / 4, 4) << 20;
+  return groups <= 1 ? 0 : groups <= 3 ? 1ull << 18 : (groups <= 16 ? 1ull : 3ull) << 20;
 }
 
 // The addresses are device addresses: they are only ever offset here, never dereferenced, and
