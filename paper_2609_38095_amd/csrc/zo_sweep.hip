@@ -239,9 +239,10 @@ __device__ __forceinline__ float* shared_table(float* tab, uint32_t g) {
 // and the coefficient reads are uniform (scalar loads), and the sign of slot s is an XOR of the
 // coefficient's sign bit with bit s of ~b. A workgroup of BLOCK threads builds BLOCK / 256
 // groups at a time: thread b + 256 m writes entry b of groups m, m + BLOCK / 256, ... The count is a
-// constant of the loop from three groups on (with the run-time one, K = 64 and 96 on 270 M bf16
-// weights take 445 and 710 us against 377 and 582); with one group, unrolling the loop away slows the
-// streaming fp32 update (K = 5, 5.2 GB: 1,601 -> 1,693 us), with two it costs fp32 0 to 2%.
+// constant of the loop (with the run-time one, K = 64 and 96 on 270 M bf16 weights take 445 and 710 us
+// against 377 and 582), except where the sweep around the unrolled loop is scheduled worse: one
+// group on spread tables (fp32, K = 5, 5.2 GB: 1,601 -> 1,693 us), two groups (fp32 0 to 2%) and five (bf16,
+// K = 37, 0.55 GB: 256 -> 281 us).
 template <int NG, int C, int BLOCK>
 __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32_t k_base, uint32_t K,
                                              uint32_t n_groups, float lr, uint32_t fold_g, const Probe& fold) {
@@ -251,7 +252,8 @@ __device__ __forceinline__ void build_tables(float* tab, const Coefs& cf, uint32
 #pragma unroll
   for (int s = 0; s < 8; ++s) flip[s] = ((~b) << (31 - s)) & 0x80000000u;
   const uint32_t g_first = k_base / 8;
-  for (uint32_t g = threadIdx.x >> 8; g < (NG > 2 ? NG : n_groups); g += BLOCK / 256) {
+  constexpr bool kUnrolled = NG == 1 ? C == 0 : NG > 2 && NG != 5;
+  for (uint32_t g = threadIdx.x >> 8; g < (kUnrolled ? NG : n_groups); g += BLOCK / 256) {
     float v[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
